@@ -5,11 +5,10 @@
 //
 // Tiling: a workgroup of 8 waves owns a 256 x 256 tile of C; each wave owns 128 x 64 as 8 x 4
 // blocks of v_mfma_f32_16x16x32_bf16 (which sustains about 98% of the matrix cores' peak on this
-// part against about 86% for the 32x32x16 form). K advances 64 at a time through a ring of two
-// LDS slabs that the buffer unit fills directly (buffer loads that write LDS: no registers
-// staged, no LDS store instructions): the next slab is requested right after the barrier that
-// frees its buffer and is multiplied one slab later. Within a slab the fragments of the second
-// 32-step are read while the first is multiplied.
+// part against about 86% for the 32x32x16 form). K advances 64 at a time through two LDS slabs
+// that the buffer unit fills directly (buffer loads that write LDS: no registers staged, no LDS
+// store instructions). gemm_bf16_kernel says how the loads, the fragment reads and the MFMAs of
+// consecutive slabs, and of consecutive tiles, overlap.
 //
 // LDS slab: 512 rows (A's 256, then B's) of 64 bf16 = 128 bytes, unpadded because one
 // buffer->LDS instruction fills 1 KiB contiguously. The 16-byte chunk c of row r is stored at
@@ -41,81 +40,90 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t make_rsrc(const void* base, ui
   return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), 0, (int)bytes, kRsrcWord3);
 }
 
-// Bytes of an R x K row-major matrix (row stride ld elements of `es` bytes) from row r0 on,
-// clamped to the 32-bit range of a buffer resource (offsets used stay below it).
-__device__ __forceinline__ uint32_t span_bytes(int64_t R, int64_t r0, int64_t K, int64_t ld,
-                                               int es) {
+// Bytes of an R x K row-major matrix (row stride ld elements of 2 bytes) from row r0 on, K
+// rounded up to whole 16-byte chunks (an aligned chunk that holds a valid element cannot cross
+// into an unmapped page), clamped to kOobBase: the offsets of a tile's 256 rows stay below it
+// (ld <= 2^22), and kOobBase plus any row offset lies beyond every resource. Rows past R lie
+// beyond theirs. A load beyond its resource returns zeros.
+constexpr uint32_t kOobBase = 0x80000000u;
+__device__ __forceinline__ uint32_t span_bytes(int64_t R, int64_t r0, int64_t K, int64_t ld) {
   if (r0 >= R) return 0;
-  const int64_t b = ((R - r0 - 1) * ld + K) * es;
-  return b > 0xFFFFFFFFll ? 0xFFFFFFFFu : (uint32_t)b;
+  const int64_t b = ((R - r0 - 1) * ld + (K + 7) / 8 * 8) * 2;
+  return b > (int64_t)kOobBase ? kOobBase : (uint32_t)b;
 }
 
-// Logical work unit -> (split, tile). Logically the smaller operand's tile index runs fastest:
-// the larger operand's panel is then shared by consecutive units and streamed from HBM about
-// once.
-template <int BM, int BN>
-__device__ __forceinline__ void unit_tile(const GemmArgs& g, int64_t lin, int64_t& tm,
-                                          int64_t& tn, int64_t& split) {
-  const int64_t mt = (g.M + BM - 1) / BM, nt = (g.N + BN - 1) / BN;
+// Logical work unit -> (split, tile). The smaller dimension's tiles run fastest, in groups of at
+// most kTileGroup of them, then the larger dimension, then the next group: the 32 units in
+// flight on an XCD form about 8 x 4 tiles and share their operand panels in its L2. Loads alone
+// (no arithmetic, one slab ahead) of the 4096 x 151936 x 2048 product took 1.19 us per slab in
+// groups of 8 against 1.33 us with all 16 row tiles fastest.
+constexpr uint32_t kTileGroup = 8;
+__device__ __forceinline__ void unit_tile(const GemmArgs& g, uint32_t lin, uint32_t& tm,
+                                          uint32_t& tn, uint32_t& split) {
+  const uint32_t mt = (uint32_t)((g.M + kGemmTile - 1) / kGemmTile);
+  const uint32_t nt = (uint32_t)((g.N + kGemmTile - 1) / kGemmTile);
   split = lin / (mt * nt);
-  const int64_t t = lin % (mt * nt);
-  if (g.m_fastest) {
-    tm = t % mt;
-    tn = t / mt;
-  } else {
-    tn = t % nt;
-    tm = t / nt;
-  }
+  uint32_t t = lin - split * (mt * nt);
+  const uint32_t few = g.m_fastest ? mt : nt, many = g.m_fastest ? nt : mt;
+  const uint32_t groups = (few + kTileGroup - 1) / kTileGroup;
+  const uint32_t per = (few + groups - 1) / groups;   // tiles of the smaller dimension per group
+  const uint32_t gi = t / (per * many);
+  t -= gi * (per * many);
+  const uint32_t h = few - gi * per < per ? few - gi * per : per;
+  const uint32_t hi = t / h, lo = gi * per + (t - hi * h);
+  tm = g.m_fastest ? lo : hi;
+  tn = g.m_fastest ? hi : lo;
 }
 
 // Consecutive workgroup ids go to the 8 XCDs in turn and each XCD has an L2 of its own, so XCD
 // x is given the contiguous run [xcd_first(x), xcd_first(x) + xcd_count(x)) of the n units.
-__device__ __forceinline__ int64_t xcd_count(int64_t n, int x) {
+__device__ __forceinline__ uint32_t xcd_count(uint32_t n, uint32_t x) {
   return n / kGemmQueues + (x < n % kGemmQueues ? 1 : 0);
 }
-__device__ __forceinline__ int64_t xcd_first(int64_t n, int x) {
-  const int64_t per = n / kGemmQueues, rem = n % kGemmQueues;
+__device__ __forceinline__ uint32_t xcd_first(uint32_t n, uint32_t x) {
+  const uint32_t per = n / kGemmQueues, rem = n % kGemmQueues;
   return x < rem ? x * (per + 1) : rem * (per + 1) + (x - rem) * per;
 }
 
-// One workgroup per unit: workgroup id -> unit.
-__device__ __forceinline__ int64_t unit_of_workgroup() {
-  const int64_t nwg = (int64_t)gridDim.x, id = blockIdx.x;
-  return xcd_first(nwg, (int)(id % kGemmQueues)) + id / kGemmQueues;
-}
-
-// Work queues (thread 0 of a persistent workgroup): the next unit of the home XCD's run, then
-// of the other XCDs' runs in turn; -1 when all are taken. `tried` counts the runs found empty
-// (kept across calls), so a workgroup makes at most kGemmQueues failed attempts in all.
-__device__ __forceinline__ int64_t next_unit(const GemmArgs& g, int home, int& tried) {
-  while (tried < kGemmQueues) {
-    const int x = (home + tried) % kGemmQueues;
-    const int i = atomicAdd(&g.queue[x], 1);
-    if (i < xcd_count(g.units, x)) return xcd_first(g.units, x) + i;
+// Work queues (thread 0 of a workgroup): the next unit of the home XCD's run, then of the other
+// XCDs' runs in turn; -1 when all are taken, or without a queue. The first units of a run go to
+// the workgroups of that XCD by their index (xcd_count(gridDim.x, x) of them); the counter hands
+// out the others. `tried` counts the runs found empty (kept across calls), so a workgroup makes
+// at most kGemmQueues failed attempts in all.
+__device__ __forceinline__ int next_unit(const GemmArgs& g, uint32_t home, uint32_t& tried) {
+  if (!g.queue) return -1;
+  while (tried < (uint32_t)kGemmQueues) {
+    const uint32_t x = (home + tried) % kGemmQueues;
+    const uint32_t i = xcd_count(gridDim.x, x) + (uint32_t)atomicAdd(&g.queue[x], 1);
+    if (i < xcd_count((uint32_t)g.units, x)) return (int)(xcd_first((uint32_t)g.units, x) + i);
     ++tried;
   }
   return -1;
 }
 
-// Waits until at most N of this wave's buffer operations are outstanding (gfx9 encoding: vmcnt
-// in bits 3:0 and 15:14; expcnt and lgkmcnt left at their maxima).
-template <int N>
-__device__ __forceinline__ void wait_vmcnt() {
-  __builtin_amdgcn_s_waitcnt((N & 15) | ((N >> 4) << 14) | 0x0F70);
+// Two 16-byte buffer loads that write LDS: lane l stores at bytes lds + 16 l and lds + 8192 +
+// 16 l (lds is the same for the whole wave). Counted by vmcnt. The voff are range-checked against
+// the resource, soff is not. They are written in assembly, and have no register output, because
+// the compiler puts a full vmcnt wait between such a load and a later LDS read that it cannot
+// tell apart; the waits here are explicit and counted. (m0 needs one wait state before its use,
+// and an SGPR that a vector instruction wrote five, which the compiler does not insert ahead of
+// assembly; it sets m0 right before each use of its own.)
+__device__ __forceinline__ void load_lds16x2(__amdgpu_buffer_rsrc_t r, uint32_t lds,
+                                             uint32_t voff0, uint32_t voff1, uint32_t soff) {
+  asm volatile(
+      "s_mov_b32 m0, %0\n\ts_nop 3\n\tbuffer_load_dwordx4 %2, %4, %5 offen lds\n\t"
+      "s_mov_b32 m0, %1\n\ts_nop 0\n\tbuffer_load_dwordx4 %3, %4, %5 offen lds"
+      ::"s"(lds), "s"(lds + 8192), "v"(voff0), "v"(voff1), "s"(r), "s"(soff)
+      : "memory");
 }
 
-// 16-byte buffer load that writes LDS: lane l stores at lds_wave + 16 l bytes (lds_wave is the
-// same for the whole wave). Counted by vmcnt. (The builtin sits in a device function of its own:
-// inside a lambda it loses its host-side declaration.)
-__device__ __forceinline__ void load_lds16(__amdgpu_buffer_rsrc_t r, __bf16* lds_wave,
-                                           uint32_t voff) {
-  __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (__attribute__((address_space(3))) void*)lds_wave,
-                                           16, voff, 0, 0, 0);
-}
-
-// Workgroup barrier after this wave's LDS operations. __syncthreads() would also wait for every
-// buffer->LDS load still in flight; the slab waits are explicit (wait_vmcnt) instead. The memory
+// Workgroup barrier once this wave's LDS reads have landed and at most N of its vector-memory
+// operations are outstanding. __syncthreads() would wait for every load in flight. The memory
 // clobber keeps the compiler from moving LDS accesses across it.
+template <int N>
+__device__ __forceinline__ void wait_barrier() {
+  asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(N) : "memory");
+}
 __device__ __forceinline__ void lds_barrier() {
   asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
 }
@@ -123,81 +131,12 @@ __device__ __forceinline__ void lds_barrier() {
 constexpr int kWaves = (kGemmTile / kGemmWaveM) * (kGemmTile / kGemmWaveN);  // 8
 constexpr int kThreads = kWaves * 64;
 constexpr int kTm = kGemmWaveM / 16, kTn = kGemmWaveN / 16;                 // 8 x 4 blocks
-constexpr int kSlab = 2 * kGemmTile * kGemmBK;       // bf16 per LDS slab (A rows, B rows)
-constexpr int kLoads = 2 * kGemmTile * (kGemmBK / 8) / kThreads;  // 16-byte units per lane
-constexpr int kALoads = kLoads / 2;                  // the first half fill A's rows
-static_assert(kGemmBK == 64 && kThreads * 8 / 64 * kALoads == kGemmTile,
-              "a slab row is 8 chunks; each load covers 64 rows");
-
-// One slab of MFMAs for a wave's kTm x kTn blocks: two 32-steps, the fragments of the second
-// read from LDS while the first is multiplied. fa(i, s) / fb(j, s) give fragment addresses.
-//   SPLIT = false: each step's 12 reads have landed before the next step's are issued (the LDS
-//     counter tracks at most 15 reads; with 24 in flight the compiler would wait for all of
-//     them before the first MFMA).
-//   SPLIT = true: the first step's fragments are read B first, then A row by row, and each row
-//     of MFMAs waits only for its own fragments (the compiler's counted LDS waits), so the
-//     first MFMAs after the slab barrier start once five reads have landed. The second step's
-//     12 reads are issued after row kSplitRow of the first step, which keeps every wait within
-//     the counter's 15.
-constexpr int kSplitRow = 4;
-template <bool SPLIT, class FA, class FB>
-__device__ __forceinline__ void mfma_slab(f32x4 (&acc)[kTm][kTn], FA fa, FB fb) {
-  static_assert(kGemmBK == 64, "two 32-steps per slab");
-  static_assert((kTm - 1 - kSplitRow) + kTm + kTn <= 15, "waits stay within the LDS counter");
-  bf16x8 a0[kTm], b0[kTn], a1[kTm], b1[kTn];
-  auto row = [&](int i, const bf16x8(&a)[kTm], const bf16x8(&b)[kTn]) {
-#pragma unroll
-    for (int j = 0; j < kTn; ++j)
-      acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(b[j], a[i], acc[i][j], 0, 0, 0);
-  };
-  // SPLIT reads B first (every row of MFMAs needs all of B); otherwise A first
-  auto read = [&](int s, bf16x8(&a)[kTm], bf16x8(&b)[kTn]) {
-    if constexpr (SPLIT) {
-#pragma unroll
-      for (int j = 0; j < kTn; ++j) b[j] = *(const bf16x8*)fb(j, s);
-    }
-#pragma unroll
-    for (int i = 0; i < kTm; ++i) a[i] = *(const bf16x8*)fa(i, s);
-    if constexpr (!SPLIT) {
-#pragma unroll
-      for (int j = 0; j < kTn; ++j) b[j] = *(const bf16x8*)fb(j, s);
-    }
-  };
-  read(0, a0, b0);
-  if constexpr (SPLIT) {
-    __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-    for (int i = 0; i < kSplitRow; ++i) {
-      row(i, a0, b0);
-      __builtin_amdgcn_sched_barrier(0);
-    }
-    read(1, a1, b1);
-    __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-    for (int i = kSplitRow; i < kTm; ++i) {
-      row(i, a0, b0);
-      __builtin_amdgcn_sched_barrier(0);
-    }
-#pragma unroll
-    for (int i = 0; i < kTm; ++i) {
-      row(i, a1, b1);
-      __builtin_amdgcn_sched_barrier(0);
-    }
-  } else {
-    __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0); vmcnt and expcnt at their maxima
-    __builtin_amdgcn_sched_barrier(0);
-    read(1, a1, b1);
-    __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-    for (int i = 0; i < kTm; ++i) row(i, a0, b0);
-    __builtin_amdgcn_sched_barrier(0);
-    __builtin_amdgcn_s_waitcnt(0xC07F);
-    __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-    for (int i = 0; i < kTm; ++i) row(i, a1, b1);
-    __builtin_amdgcn_sched_barrier(0);
-  }
-}
+constexpr int kPieceBytes = kGemmTile / 2 * kGemmBK * 2;  // half of an operand's rows of a slab
+constexpr int kOpBytes = 4 * kPieceBytes;                 // an operand's rows, both slabs
+constexpr int kPieceLoads = kPieceBytes / (kThreads * 16);  // loads per wave and piece: 2
+constexpr int kGroupLoads = 2 * kPieceLoads;             // two pieces are requested together
+static_assert(kGemmBK == 64 && kWaves == 8 && kTm == 8 && kTn == 4 && kPieceLoads == 2,
+              "the piece maps below");
 
 // Epilogue of a tile: lane holds C[m][n .. n + 3] for m = m-block row + lane % 16,
 // n = n-block column + 4 (lane / 16); 16-byte stores where the row allows them.
@@ -306,21 +245,16 @@ __device__ __forceinline__ float grad_value(const GradParams& p, float z, int64_
 // Row-loss epilogue kEpiGrad: grad_value of every logit of the tile, rounded to bf16 (nearest
 // even) into G.
 __device__ __forceinline__ void grad_tile(const GemmArgs& g, const f32x4 (&acc)[kTm][kTn],
-                                          int64_t m0, int64_t n0) {
+                                          int64_t m0, int64_t n0,
+                                          const GradParams (&gp)[kGemmTile]) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int wm = wave / (kGemmTile / kGemmWaveN), wn = wave % (kGemmTile / kGemmWaveN);
   const int fr = lane & 15, fq = lane >> 4;
-  GradParams ps[kTm];  // every row's parameters requested before the first is used
-#pragma unroll
-  for (int i = 0; i < kTm; ++i) {
-    const int64_t m = m0 + wm * kGemmWaveM + i * 16 + fr;
-    ps[i] = m < g.M ? g.e.gp[m] : GradParams{INFINITY, 0, 0.f, -1};
-  }
 #pragma unroll
   for (int i = 0; i < kTm; ++i) {
     const int64_t m = m0 + wm * kGemmWaveM + i * 16 + fr;
     if (m >= g.M) continue;
-    const GradParams p = ps[i];
+    const GradParams p = gp[wm * kGemmWaveM + i * 16 + fr];
     __bf16* grow = g.e.G + m * g.e.ldg;
 #pragma unroll
     for (int j = 0; j < kTn; ++j) {
@@ -340,142 +274,265 @@ __device__ __forceinline__ void grad_tile(const GemmArgs& g, const f32x4 (&acc)[
   }
 }
 
-// The (tm, tn) tile of C over split `split` of the contraction, by the whole workgroup. The
-// caller puts a barrier between two tiles of one workgroup (the last slab's reads must end
-// before the next tile refills LDS; with an empty K range there is no barrier inside).
-// The sampled ids of the tile's rows for kEpiLse, loaded into LDS before the contraction (the
-// K loop's barriers make them visible; reading them in the epilogue would put a load latency
-// after every tile).
+// What the epilogue needs of a tile's rows, in LDS before the tile's contraction ends (loading
+// it in the epilogue would put a load latency after every tile).
+template <int EPI>
 struct EpiRows {
-  int y[kGemmTile];            // sampled id, or -1 when outside [0, N)
+  int y[kGemmTile];            // kEpiLse, kEpiLseStore: sampled id, or -1 when outside [0, N)
 };
+template <>
+struct EpiRows<kEpiGrad> {
+  GradParams gp[kGemmTile];
+};
+template <>
+struct EpiRows<kEpiStore> {};
 
-template <bool BETA, int EPI, bool SPLIT>
-__device__ __forceinline__ void gemm_tile(const GemmArgs& g, int64_t tm, int64_t tn,
-                                          int64_t split, __bf16 (&lds)[2 * kSlab], EpiRows& er) {
-  constexpr int BM = kGemmTile, BN = kGemmTile, BK = kGemmBK;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int wm = wave / (BN / kGemmWaveN), wn = wave % (BN / kGemmWaveN);
-  const int64_t m0 = tm * BM, n0 = tn * BN;
-  const int64_t kbeg = split * g.k_split;
-  const int64_t kend = kbeg + g.k_split < g.K ? kbeg + g.k_split : g.K;
-  const __bf16* A = static_cast<const __bf16*>(g.A) + m0 * g.lda;
-  const __bf16* B = static_cast<const __bf16*>(g.B) + n0 * g.ldb;
-  const __amdgpu_buffer_rsrc_t ra = make_rsrc(A, span_bytes(g.M, m0, g.K, g.lda, 2));
-  const __amdgpu_buffer_rsrc_t rb = make_rsrc(B, span_bytes(g.N, n0, g.K, g.ldb, 2));
+// The operands of one unit: resources at its tile's first rows, and its contraction range.
+struct UnitSrc {
+  __amdgpu_buffer_rsrc_t a, b;
+  uint32_t m0, n0, split;
+  int kbeg, kend;
+};
+__device__ __forceinline__ UnitSrc unit_src(const GemmArgs& g, int u) {
+  UnitSrc s;
+  uint32_t tm = 0, tn = 0;
+  s.split = 0;
+  if (u >= 0) unit_tile(g, (uint32_t)u, tm, tn, s.split);
+  s.m0 = tm * kGemmTile;
+  s.n0 = tn * kGemmTile;
+  s.kbeg = (int)(s.split * g.k_split);
+  s.kend = u < 0 ? s.kbeg : (int)(s.kbeg + g.k_split < g.K ? s.kbeg + g.k_split : g.K);
+  // (u < 0: empty resources, so that the loads ahead of the last tile read nothing)
+  s.a = make_rsrc(static_cast<const __bf16*>(g.A) + (int64_t)s.m0 * g.lda,
+                  u < 0 ? 0 : span_bytes(g.M, s.m0, g.K, g.lda));
+  s.b = make_rsrc(static_cast<const __bf16*>(g.B) + (int64_t)s.n0 * g.ldb,
+                  u < 0 ? 0 : span_bytes(g.N, s.n0, g.K, g.ldb));
+  return s;
+}
 
-  // Load j of a wave fills the slab's 16-byte units (8 j + wave) 64 + lane: slab row
-  // r = 64 j + 8 wave + lane / 8 (A rows, then B rows from j = kALoads on), stored chunk
-  // lane % 8, holding logical chunk (lane % 8) ^ (r & 7) = (lane % 8) ^ (lane / 8 % 8).
-  // Rows past M or N read as zero through the buffer range check.
-  const int lchunk = (lane & 7) ^ ((lane >> 3) & 7);
-  const int64_t r0 = wave * 8 + (lane >> 3);
-  const uint32_t offa = (uint32_t)((r0 * g.lda + lchunk * 8) * 2);
-  const uint32_t offb = (uint32_t)((r0 * g.ldb + lchunk * 8) * 2);
-  const uint32_t stepa = (uint32_t)(64 * g.lda * 2), stepb = (uint32_t)(64 * g.ldb * 2);
-  auto off = [&](int j) { return j < kALoads ? offa + j * stepa : offb + (j - kALoads) * stepb; };
-  const int64_t nk = kend > kbeg ? (kend - kbeg + BK - 1) / BK : 0;
-  auto issue = [&](int64_t kt) {
-    __bf16* st = lds + (int)(kt & 1) * kSlab;
-    const int64_t k0 = kbeg + kt * BK;
-    const uint32_t ko = (uint32_t)(k0 * 2);
-    if (k0 + BK <= kend) {
+// The products. A workgroup works through units (tiles, or a tile's share of a split
+// contraction): its own first one, then with a queue further ones until all are taken.
+//
+// A slab of LDS is four pieces of 16 KiB: A0, A1 (per wave row the first and second 64 of its
+// 128 tile rows) and B0, B1 (per wave column the first and second 32 of its 64 columns). A wave
+// multiplies a slab in four phases of 16 MFMAs, one per pair of pieces, in an order that swaps
+// the parts of B0 and B1 from slab to slab:
+//
+//   even slab (buffer 0):  A0 B0 | A0 B1 || A1 B1 | A1 B0 ||
+//   odd slab  (buffer 1):  A0 B1 | A0 B0 || A1 B0 | A1 B1 ||
+//
+// so the fragments of a phase are always read from LDS one phase or more ahead, into registers
+// whose last use has passed (A0, A1: 32 registers each, B0, B1: 16 each), and no MFMA waits for
+// a read issued after a barrier. A barrier (||) every two phases frees two pieces, which are
+// requested for the slab two ahead at once; they are waited for three such requests later (six
+// phases, 1.5 slabs), and the two newer requests stay in flight (vmcnt(2 * kGroupLoads)). Loads
+// alone, one slab ahead, take 1.2-1.5 us per slab here, and 0.92-1.16 us two slabs ahead.
+// The same stream runs on into the next tile: its first two slabs are requested during the last
+// two of this one, so the epilogue runs with them in flight. (Past the last unit, and past the
+// end of the contraction, the loads are out of range and return zeros.) Contractions are
+// multiplied in pairs of slabs.
+//
+// What bounds it: the card's power. With operands of zeros the same loop runs at 2.36 GHz and
+// 2110-2230 TFLOP/s (2290-2390 clocks per slab, 2048 of them MFMAs); with random operands the
+// clock falls to 1.67-1.71 GHz (1423-1535 TFLOP/s without an epilogue). Products of the rollout
+// batch, before (one slab ahead, every fragment read behind the slab's barrier) and now:
+// logits with pairs, 4096 x 151936 x 2048, 2.07 and 1.84 ms; with the stored chunk 2.65 and
+// 2.42 ms; dL/dh, 4096 x 2048 x 151936, 1.97 and 1.72 ms; dL/dW, 151936 x 2048 x 16384, 8.62
+// and 7.49 ms.
+template <bool BETA, int EPI>
+__global__ __launch_bounds__(kThreads) void gemm_bf16_kernel(const GemmArgs g) {
+  // A's pieces (slab 0: A0, A1, slab 1: A0, A1), then B's: every fragment of an operand lies
+  // within the 16-bit offset of one address
+  __shared__ __attribute__((aligned(1024))) char lds[2 * kOpBytes];
+  __shared__ EpiRows<EPI> er[2];   // of this unit and of the next
+  __shared__ int sh_unit[2];       // the unit after this one
+  constexpr bool kLse = EPI == kEpiLse || EPI == kEpiLseStore;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wm = wave / (kGemmTile / kGemmWaveN), wn = wave % (kGemmTile / kGemmWaveN);
+  const uint32_t lds0 =
+      (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)lds + wave * 1024;
+
+  const uint32_t home = blockIdx.x % kGemmQueues;
+  uint32_t tried = 0;
+  int u = (int)(xcd_first((uint32_t)g.units, home) + blockIdx.x / kGemmQueues);
+
+  // Load j (0, 1) of a piece fills the 16-byte units (8 j + wave) 64 + lane of its 128 slab rows:
+  // slab row 64 j + 8 wave + lane / 8, stored chunk lane % 8, holding logical chunk (lane % 8) ^
+  // (row & 7). Slab rows to tile rows: a piece holds, per wave row (column) of the tile, 64 (32)
+  // of its rows (columns), so that a wave's tile stays contiguous: piece h's row 64 j + x of A is
+  // tile row 128 j + 64 h + x, row 32 c + x of B tile row 64 c + 32 h + x.
+  const int lchunk8 = ((lane & 7) ^ ((lane >> 3) & 7)) * 8;
+  const uint32_t va = (uint32_t)(((wave * 8 + (lane >> 3)) * g.lda + lchunk8) * 2);
+  const uint32_t vb =
+      (uint32_t)(((wave / 4 * 64 + wave % 4 * 8 + (lane >> 3)) * g.ldb + lchunk8) * 2);
+  const uint32_t sa = (uint32_t)(64 * g.lda * 2), sb = (uint32_t)(32 * g.ldb * 2);
+  // operand op (0: A, 1: B), piece h, of the slab at k into buffer b. Chunks at or past kend read
+  // as zero; one that straddles kend is cleared by fix().
+  auto load = [&](int op, int h, int b, const UnitSrc& s, int k) {
+    const uint32_t step = op ? sb : sa;
+    const uint32_t v = (lchunk8 < s.kend - k ? (op ? vb : va) : kOobBase) + h * step;
+    load_lds16x2(op ? s.b : s.a, lds0 + op * kOpBytes + (2 * b + h) * kPieceBytes, v,
+                 v + (op ? 4 : 2) * step, (uint32_t)(k * 2));
+  };
+  // Fragment addresses: lane holds row 16 i + lane % 16 of its piece, logical chunk
+  // 4 s + lane / 16; a block's first row is a multiple of 16, so the swizzle is lane & 7.
+  const int fr = lane & 15, fq = lane >> 4, sw = lane & 7;
+  const char* fa[2];
+  const char* fb[2];
 #pragma unroll
-      for (int j = 0; j < kLoads; ++j)
-        load_lds16(j < kALoads ? ra : rb, st + (j * kWaves + wave) * 512, off(j) + ko);
-    } else {
-      // the last slab of the range goes through registers: zero past kend, and a vector that
-      // straddles kend is read element by element (a 16-byte buffer load that is partly
-      // outside the resource returns zeros)
+  for (int s = 0; s < 2; ++s) {
+    const int c = ((4 * s + fq) ^ sw) * 16;
+    fa[s] = lds + (wm * 64 + fr) * 128 + c;
+    fb[s] = lds + kOpBytes + (wn * 32 + fr) * 128 + c;
+  }
+  bf16x8 a0[kTm / 2][2], a1[kTm / 2][2], b0[kTn / 2][2], b1[kTn / 2][2];
+  auto read_a = [&](bf16x8(&f)[kTm / 2][2], int h, int b, int q) {
+    f[q % 4][q / 4] = *(const bf16x8*)(fa[q / 4] + (2 * b + h) * kPieceBytes + (q % 4) * 2048);
+  };
+  auto read_b = [&](bf16x8(&f)[kTn / 2][2], int h, int b, int q) {
+    f[q % 2][q / 2] = *(const bf16x8*)(fb[q / 2] + (2 * b + h) * kPieceBytes + (q % 2) * 2048);
+  };
+  f32x4 acc[kTm][kTn];
+  // One phase: the MFMAs of an A piece with a B piece, a fragment read (q = 0..7, if any) ahead of
+  // each group of two, the loads of a piece ahead of the last; the fences keep that order.
+  auto phase = [&](int ha, int hb, const bf16x8(&xa)[kTm / 2][2], const bf16x8(&xb)[kTn / 2][2],
+                   auto read, auto loads) {
 #pragma unroll
-      for (int j = 0; j < kLoads; ++j) {
-        const __amdgpu_buffer_rsrc_t rs = j < kALoads ? ra : rb;
-        const uint32_t o = off(j) + ko;
-        const int64_t k = k0 + lchunk * 8;
-        bf16x8 e{};
-        if (k + 8 <= kend) {
-          e = __builtin_bit_cast(bf16x8, __builtin_amdgcn_raw_buffer_load_b128(rs, o, 0, 0));
-        } else if (k < kend) {
-          for (int i = 0; i < 8; ++i)
-            if (k + i < kend)
-              e[i] = __builtin_bit_cast(
-                  __bf16, (unsigned short)__builtin_amdgcn_raw_buffer_load_b16(rs, o + 2 * i, 0, 0));
-        }
-        *(bf16x8*)(st + ((j * kWaves + wave) * 64 + lane) * 8) = e;
-      }
+    for (int q = 0; q < 8; ++q) {
+      const int s = q / 4, i = q % 4;
+      read(q);
+      if (q == 7) loads();
+#pragma unroll
+      for (int j = 0; j < kTn / 2; ++j)
+        acc[ha * 4 + i][hb * 2 + j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+            xb[j][s], xa[i][s], acc[ha * 4 + i][hb * 2 + j], 0, 0, 0);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  };
+  // Clears the elements at and past K of the slab in buffer b whose last chunk straddles K.
+  // (Everything outstanding is waited for first: this is the last slab of a contraction whose
+  // length is not a multiple of 8.)
+  auto fix = [&](int b, int kend) {
+    wait_barrier<0>();
+    const int c = (kend % kGemmBK) / 8;
+    char* p = lds + tid / 256 * kOpBytes + b * 2 * kPieceBytes + tid % 256 * 128 +
+              ((c ^ (tid & 7)) * 16);   // a chunk of each of the slab's 512 rows
+    bf16x8 e = *(const bf16x8*)p;
+#pragma unroll
+    for (int x = 0; x < 8; ++x)
+      if (x >= kend % 8) e[x] = (__bf16)0.f;
+    *(bf16x8*)p = e;
+    lds_barrier();
+  };
+  auto tail_slab = [](const UnitSrc& s) {   // the slab that fix() is for, or -1
+    return s.kend % 8 ? (s.kend - s.kbeg) / kGemmBK : -1;
+  };
+  // requests for the epilogue's inputs of unit s's rows, and their store to LDS
+  auto epi_id = [&](const UnitSrc& s) -> int64_t {
+    const int64_t m = (int64_t)s.m0 + tid;
+    return kLse && tid < kGemmTile && m < g.M ? g.e.ids[m] : -1;
+  };
+  auto epi_gp = [&](const UnitSrc& s) -> GradParams {
+    const int64_t m = (int64_t)s.m0 + tid;
+    return EPI == kEpiGrad && tid < kGemmTile && m < g.M ? g.e.gp[m]
+                                                         : GradParams{INFINITY, 0, 0.f, -1};
+  };
+  auto epi_put = [&](EpiRows<EPI>& r, int64_t y, const GradParams& p) {
+    if (tid < kGemmTile) {
+      if constexpr (kLse) r.y[tid] = (y >= 0 && y < g.N) ? (int)y : -1;
+      if constexpr (EPI == kEpiGrad) r.gp[tid] = p;
     }
   };
 
-  f32x4 acc[kTm][kTn];
+  UnitSrc cur = unit_src(g, u);
+  // the first two slabs, in the order in which the stream requests pieces
 #pragma unroll
-  for (int i = 0; i < kTm; ++i)
+  for (int b = 0; b < 2; ++b) {
+    const int k = cur.kbeg + b * kGemmBK;
+    load(0, 0, b, cur, k);
+    load(1, b, b, cur, k);
+    load(1, 1 - b, b, cur, k);
+    load(0, 1, b, cur, k);
+  }
+  epi_put(er[0], epi_id(cur), epi_gp(cur));
+  if (tid == 0) sh_unit[0] = next_unit(g, home, tried);
+  wait_barrier<0>();
+  if (tail_slab(cur) == 0) fix(0, cur.kend);
+
+  for (int p = 0;; p ^= 1) {
 #pragma unroll
-    for (int j = 0; j < kTn; ++j) acc[i][j] = f32x4{};
-
-  // the epilogue's per-row inputs: requested now, stored to LDS once the first slab has landed
-  const int64_t mrow = m0 + tid;
-  constexpr bool kLse = EPI == kEpiLse || EPI == kEpiLseStore;
-  const bool erow = kLse && tid < kGemmTile && mrow < g.M;
-  int64_t ey = -1;
-  if (erow) ey = g.e.ids[mrow];
-  // a fragment row is a multiple of 16 plus lane % 16, so its swizzle is lane & 7
-  const int fr = lane & 15, fq = lane >> 4, sw = lane & 7;
-  if (nk > 0) issue(0);
-  // (the ids were requested before the first slab, so this waits for them alone; the first
-  // slab's barrier makes them visible, and a loop free of first-iteration code keeps the
-  // compiler from peeling it into a copy that spills)
-  if (kLse && tid < kGemmTile) er.y[tid] = (ey >= 0 && ey < g.N) ? (int)ey : -1;
-  for (int64_t kt = 0; kt < nk; ++kt) {
-    wait_vmcnt<0>();  // this wave's part of slab kt is in LDS
-    lds_barrier();    // every wave's is, and every wave is done with slab kt - 1's buffer
-    if (kt + 1 < nk) issue(kt + 1);
-    const __bf16* st = lds + (int)(kt & 1) * kSlab;
-    const __bf16* la = st + (wm * kGemmWaveM + fr) * BK;
-    const __bf16* lb = st + (BM + wn * kGemmWaveN + fr) * BK;
-    mfma_slab<SPLIT>(acc, [&](int i, int s) { return la + i * 16 * BK + ((4 * s + fq) ^ sw) * 8; },
-              [&](int j, int s) { return lb + j * 16 * BK + ((4 * s + fq) ^ sw) * 8; });
-  }
-
-  if (kLse) {
-    if (n0 + kGemmTile <= g.N)
-      lse_tile<true>(g, acc, m0, n0, tn, er.y);
-    else
-      lse_tile<false>(g, acc, m0, n0, tn, er.y);
-  }
-  if (EPI == kEpiGrad)
-    grad_tile(g, acc, m0, n0);
-  else if (EPI == kEpiStore || EPI == kEpiLseStore)
-    store_tile<BETA>(g, acc, m0, n0, split);
-}
-
-template <bool BETA, bool QUEUED, int EPI = kEpiStore>
-__global__ __launch_bounds__(kThreads) void gemm_bf16_kernel(const GemmArgs g) {
-  __shared__ __attribute__((aligned(16))) __bf16 lds[2 * kSlab];
-  __shared__ int64_t unit;
-  __shared__ EpiRows er;
-  const int home = (int)(blockIdx.x % kGemmQueues);
-  int tried = 0;
-  // one unit per workgroup, or (queued) units until every queue is empty: all threads read the
-  // same `unit` and leave together
-  for (int64_t u = QUEUED ? -1 : unit_of_workgroup();;) {
-    if (QUEUED) {
-      // every wave has read the previous `unit` and is done with the previous tile's LDS (a
-      // tile with an empty K range has no barrier of its own)
-      __syncthreads();
-      if (threadIdx.x == 0) unit = next_unit(g, home, tried);
-      __syncthreads();
-      u = unit;
+    for (int q = 0; q < 8; ++q) read_a(a0, 0, 0, q);
+#pragma unroll
+    for (int q = 0; q < 4; ++q) read_b(b0, 0, 0, q);
+    const int un = __builtin_amdgcn_readfirstlane(sh_unit[p]);
+    const UnitSrc nxt = unit_src(g, un);
+    lds_barrier();   // every wave has read A0 and B0
+#pragma unroll
+    for (int i = 0; i < kTm; ++i)
+#pragma unroll
+      for (int j = 0; j < kTn; ++j) acc[i][j] = f32x4{};
+    const int tail = tail_slab(cur), tail_nxt = tail_slab(nxt);
+    const int nk = cur.kend > cur.kbeg ? (cur.kend - cur.kbeg + 2 * kGemmBK - 1) / (2 * kGemmBK) * 2
+                                       : 2;
+    for (int kt = 0; kt < nk; kt += 2) {
+      const bool last = kt + 2 >= nk;
+      UnitSrc s;     // of the slabs two ahead
+      s.a = last ? nxt.a : cur.a;
+      s.b = last ? nxt.b : cur.b;
+      s.kend = last ? nxt.kend : cur.kend;
+      const int k2 = last ? nxt.kbeg : cur.kbeg + (kt + 2) * kGemmBK, k3 = k2 + kGemmBK;
+      // even slab
+      phase(0, 0, a0, b0, [&](int q) { if (q < 4) read_b(b1, 1, 0, q); },
+            [&] { load(0, 0, 0, s, k2); });
+      phase(0, 1, a0, b1, [&](int q) { read_a(a1, 1, 0, q); },
+            [&] { load(1, 0, 0, s, k2); });
+      if (kt + 1 == tail) fix(1, cur.kend);
+      wait_barrier<2 * kGroupLoads>();
+      phase(1, 1, a1, b1, [&](int q) { read_a(a0, 0, 1, q); },
+            [&] { load(1, 1, 0, s, k2); });
+      phase(1, 0, a1, b0, [&](int q) { if (q < 4) read_b(b1, 1, 1, q); },
+            [&] { load(0, 1, 0, s, k2); });
+      wait_barrier<2 * kGroupLoads>();
+      // odd slab
+      phase(0, 1, a0, b1, [&](int q) { if (q < 4) read_b(b0, 0, 1, q); },
+            [&] { load(0, 0, 1, s, k3); });
+      phase(0, 0, a0, b0, [&](int q) { read_a(a1, 1, 1, q); },
+            [&] { load(1, 1, 1, s, k3); });
+      if (last ? tail_nxt == 0 : kt + 2 == tail) fix(0, s.kend);
+      wait_barrier<2 * kGroupLoads>();
+      phase(1, 0, a1, b0, [&](int q) { read_a(a0, 0, 0, q); },
+            [&] { load(1, 0, 1, s, k3); });
+      phase(1, 1, a1, b1, [&](int q) { if (q < 4) read_b(b0, 0, 0, q); },
+            [&] { load(0, 1, 1, s, k3); });
+      wait_barrier<2 * kGroupLoads>();
     }
-    if (u < 0) break;
-    int64_t tm, tn, split;
-    unit_tile<kGemmTile, kGemmTile>(g, u, tm, tn, split);
-    // The split fragment reads where the compiler keeps the K loop free of full vmcnt waits:
-    // in the other forms it placed a vmcnt(0) before the first step's A reads, which also
-    // waits for the next slab's loads.
-    constexpr bool kSplitReads = EPI == kEpiLse || (EPI == kEpiLseStore && QUEUED);
-    gemm_tile<BETA, EPI, kSplitReads>(g, tm, tn, split, lds, er);
-    if (!QUEUED) break;
+    // The next unit's slab 0 is in LDS and its slab 1 on the way. Its epilogue inputs, and the
+    // unit after it, are requested now and stored once this epilogue is through. (The fragments
+    // that the last phases read of it are read again above: they would cost the epilogue 48
+    // registers.)
+    const int64_t y = epi_id(nxt);
+    const GradParams gp = epi_gp(nxt);
+    int u2 = -1;
+    if (tid == 0 && un >= 0) u2 = next_unit(g, home, tried);
+    if constexpr (kLse) {
+      if ((int64_t)cur.n0 + kGemmTile <= g.N)
+        lse_tile<true>(g, acc, cur.m0, cur.n0, cur.n0 / kGemmTile, er[p].y);
+      else
+        lse_tile<false>(g, acc, cur.m0, cur.n0, cur.n0 / kGemmTile, er[p].y);
+    }
+    if constexpr (EPI == kEpiGrad) grad_tile(g, acc, cur.m0, cur.n0, er[p].gp);
+    if constexpr (EPI == kEpiStore || EPI == kEpiLseStore)
+      store_tile<BETA>(g, acc, cur.m0, cur.n0, cur.split);
+    if (un < 0) break;
+    epi_put(er[p ^ 1], y, gp);
+    if (tid == 0) sh_unit[p ^ 1] = u2;
+    u = un;
+    cur = nxt;
+    lds_barrier();
   }
+  // the (empty) loads ahead of the last unit must not outlive the workgroup's LDS
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
 }
 
 // C = alpha * sum_s P[s] (+ C): the split-K partials summed in split order.
@@ -568,21 +625,27 @@ __global__ __launch_bounds__(256) void transpose_kernel(const TransposeArgs t) {
   }
 }
 
-// Launch over `splits` splits; with g.queue, one workgroup per CU (the LDS ring allows one)
-// works through the queues.
-hipError_t launch_tiles(GemmArgs g, bool beta, int splits, int num_cu, hipStream_t stream) {
-  const int64_t mt = (g.M + kGemmTile - 1) / kGemmTile, nt = (g.N + kGemmTile - 1) / kGemmTile;
-  g.units = mt * nt * splits;
-  const int64_t grid = g.queue && num_cu < g.units ? num_cu : g.units;
-  const void* fn = g.queue ? (beta ? (const void*)&gemm_bf16_kernel<true, true>
-                                   : (const void*)&gemm_bf16_kernel<false, true>)
-                           : (beta ? (const void*)&gemm_bf16_kernel<true, false>
-                                   : (const void*)&gemm_bf16_kernel<false, false>);
+__global__ __launch_bounds__(kGemmQueues) void zero_queue_kernel(int* q) { q[threadIdx.x] = 0; }
+
+int64_t gemm_tiles(const GemmArgs& g) {
+  return ((g.M + kGemmTile - 1) / kGemmTile) * ((g.N + kGemmTile - 1) / kGemmTile);
+}
+
+// Launches `fn` over g.units units, one workgroup per CU at most (the LDS slabs allow one). With
+// more units than CUs the workgroups take them from the queues, cleared first by a kernel rather
+// than a memset node, so that the call can be graph-captured.
+hipError_t launch_units(GemmArgs g, const void* fn, int* queue, int num_cu, hipStream_t stream) {
+  g.queue = g.units > num_cu ? queue : nullptr;
+  if (g.queue) {
+    void* zargs[] = {&g.queue};
+    if (hipError_t e = hipLaunchKernel((const void*)&zero_queue_kernel, dim3(1),
+                                       dim3(kGemmQueues), zargs, 0, stream))
+      return e;
+  }
+  const int64_t grid = g.queue ? num_cu : g.units;
   void* args[] = {&g};
   return hipLaunchKernel(fn, dim3((unsigned)grid), dim3(kThreads), args, 0, stream);
 }
-
-__global__ __launch_bounds__(kGemmQueues) void zero_queue_kernel(int* q) { q[threadIdx.x] = 0; }
 
 }  // namespace
 
@@ -592,35 +655,13 @@ hipError_t launch_gemm_epi(GemmArgs g, int* queue, int num_cu, hipStream_t strea
   g.k_split = g.K > 0 ? g.K : 1;
   g.c_split_stride = 0;
   g.c_vec = g.epi == kEpiLseStore && ((uintptr_t)g.C % 16 == 0) && g.ldc % 4 == 0;
-  const int64_t mt = (g.M + kGemmTile - 1) / kGemmTile, nt = (g.N + kGemmTile - 1) / kGemmTile;
-  g.units = mt * nt;
-  g.queue = g.units > num_cu ? queue : nullptr;
-  if (g.queue) {
-    void* zargs[] = {&g.queue};
-    if (hipError_t e = hipLaunchKernel((const void*)&zero_queue_kernel, dim3(1),
-                                       dim3(kGemmQueues), zargs, 0, stream))
-      return e;
-  }
-  const int64_t grid = g.queue ? num_cu : g.units;
-  const void* fn;
-  switch (g.epi) {
-    case kEpiLse:
-      fn = g.queue ? (const void*)&gemm_bf16_kernel<false, true, kEpiLse>
-                   : (const void*)&gemm_bf16_kernel<false, false, kEpiLse>;
-      break;
-    case kEpiGrad:
-      fn = g.queue ? (const void*)&gemm_bf16_kernel<false, true, kEpiGrad>
-                   : (const void*)&gemm_bf16_kernel<false, false, kEpiGrad>;
-      break;
-    case kEpiLseStore:
-      fn = g.queue ? (const void*)&gemm_bf16_kernel<false, true, kEpiLseStore>
-                   : (const void*)&gemm_bf16_kernel<false, false, kEpiLseStore>;
-      break;
-    default:
-      return hipErrorInvalidValue;
-  }
-  void* args[] = {&g};
-  return hipLaunchKernel(fn, dim3((unsigned)grid), dim3(kThreads), args, 0, stream);
+  g.units = gemm_tiles(g);
+  const void* fn = g.epi == kEpiLse        ? (const void*)&gemm_bf16_kernel<false, kEpiLse>
+                   : g.epi == kEpiGrad     ? (const void*)&gemm_bf16_kernel<false, kEpiGrad>
+                   : g.epi == kEpiLseStore ? (const void*)&gemm_bf16_kernel<false, kEpiLseStore>
+                                           : nullptr;
+  if (!fn) return hipErrorInvalidValue;
+  return launch_units(g, fn, queue, num_cu, stream);
 }
 
 int64_t gemm_splitk_count(int64_t M, int64_t N, int64_t K, int num_cu) {
@@ -637,22 +678,15 @@ hipError_t launch_gemm_nt(GemmArgs g, bool beta, float* partial, int* queue, int
   // A is M x K, B is N x K: the smaller one's tiles run fastest
   g.m_fastest = g.M <= g.N;
   const int64_t splits = partial ? gemm_splitk_count(g.M, g.N, g.K, num_cu) : 1;
-  const int64_t units =
-      ((g.M + kGemmTile - 1) / kGemmTile) * ((g.N + kGemmTile - 1) / kGemmTile) * splits;
-  // the queues pay off once there is more than one workgroup per CU to place
-  g.queue = units > num_cu ? queue : nullptr;
-  if (g.queue) {  // a fill kernel rather than a memset node, so the call can be graph-captured
-    void* zargs[] = {&g.queue};
-    if (hipError_t e = hipLaunchKernel((const void*)&zero_queue_kernel, dim3(1),
-                                       dim3(kGemmQueues), zargs, 0, stream))
-      return e;
-  }
+  g.units = gemm_tiles(g) * splits;
+  const void* fn = beta && splits <= 1 ? (const void*)&gemm_bf16_kernel<true, kEpiStore>
+                                       : (const void*)&gemm_bf16_kernel<false, kEpiStore>;
   const bool c_aligned = ((uintptr_t)g.C % 16 == 0) && g.ldc % 4 == 0;
   if (splits <= 1) {
     g.k_split = g.K > 0 ? g.K : 1;
     g.c_split_stride = 0;
     g.c_vec = c_aligned;
-    return launch_tiles(g, beta, 1, num_cu, stream);
+    return launch_units(g, fn, queue, num_cu, stream);
   }
   // split-K: partial products into `partial` [splits][M][N], then summed in split order
   const int64_t kper = ((g.K + splits - 1) / splits + kGemmBK - 1) / kGemmBK * kGemmBK;
@@ -663,8 +697,7 @@ hipError_t launch_gemm_nt(GemmArgs g, bool beta, float* partial, int* queue, int
   p.k_split = kper;
   p.c_split_stride = g.M * g.N;
   p.c_vec = ((uintptr_t)partial % 16 == 0) && g.N % 4 == 0;
-  if (hipError_t e = launch_tiles(p, false, (int)splits, num_cu, stream))
-    return e;
+  if (hipError_t e = launch_units(p, fn, queue, num_cu, stream)) return e;
   ReduceArgs r{partial, g.C, g.M, g.N, g.ldc, g.M * g.N, (int32_t)splits, g.alpha, beta};
   const int64_t blocks = (g.M * g.N + 255) / 256;
   void* args[] = {&r};

@@ -273,6 +273,26 @@ def test_lmhead_queued_products_ragged_hidden(recompute):
         assert torch.equal(out[k], again[k]), k
 
 
+@pytest.mark.parametrize("H", [1, 7, 63, 64, 65, 71, 128, 130, 191, 193, 320, 327])
+def test_lmhead_contraction_tails(H):
+    """The products multiply pairs of 64-long slabs: contractions that end in the first, second
+    and later slabs, with an odd and an even number of them, on a whole slab, on a whole 16-byte
+    chunk and inside one (the padding of the operands' rows holds NaN). The two backward
+    products contract over 700 = 10 x 64 + 60 and, with two dL/dW groups of 69 and 2 rows, over
+    less than a chunk."""
+    b = make_lmhead_batch(71, 700, H, device=DEV, seed=13, min_len=8, max_len=40,
+                          ld_h=(H + 15) // 8 * 8, ld_w=(H + 23) // 8 * 8)
+    run_case(f"tail_H{H}", b, chunk=69)
+
+
+def test_lmhead_queued_products_straddling_chunk():
+    """More tiles than CUs with a contraction that ends inside a 16-byte chunk: every tile after
+    a workgroup's first has its last slab cleared while the tile before it is multiplied."""
+    b = make_lmhead_batch(300, 40000, 61, device=DEV, seed=17, min_len=16, max_len=96, ld_h=64,
+                          ld_w=64)
+    run_case("queued_H61", b, chunk=4096)
+
+
 @pytest.mark.parametrize("recompute", [False, True], ids=["chunked_logits", "recompute"])
 def test_lmhead_largest_vocabulary(recompute):
     """V = 2^22, the largest vocabulary the LM-head calls accept: float32 logit rows of 16 MB
