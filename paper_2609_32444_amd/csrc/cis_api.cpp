@@ -129,14 +129,28 @@ int launch_grid_stride(const void* fn, int64_t T, int block, const DeviceInfo& i
   return launch(fn, (int)(need < cap ? need : cap), block, arg, stream);
 }
 
-// Sequence operators: per-response log K into the workspace.
+// Sequence operators: per-response log K for the pre-pass `pa`, and the kernel that sums it. A
+// wave per response up to kSeqWaveLen tokens on average (a workgroup of 1024 threads would idle
+// there), else workgroups: with few long responses several for each, as far as their sums fit
+// the head of the workspace and have 2048 tokens each (two per thread).
+constexpr int64_t kSeqWaveLen = 512;
 int launch_seq_sum(const float* lp, const float* lq, const uint8_t* mask, const int64_t* ids,
                    int64_t V, const int64_t* offsets, int64_t n_seq, int64_t T, const Ws& ws,
-                   hipStream_t stream) {
-  cis::SeqSumArgs sa{lp, lq, mask, ids, offsets, reinterpret_cast<double*>(ws.base + ws.L.logK),
-                     T, n_seq, (int32_t)V};
-  const int64_t per = cis::kSeqBlock / 64;
-  return launch(cis::seq_sum_kernel(), (int)((n_seq + per - 1) / per), cis::kSeqBlock, &sa,
+                   cis::PrepassArgs* pa, hipStream_t stream) {
+  const int64_t avg = T / n_seq;
+  int64_t pieces = 1;
+  if (avg > kSeqWaveLen) {
+    const int64_t fit = cis::kSeqPieceSums / n_seq, work = avg / 2048;
+    pieces = fit < work ? fit : work;
+    if (pieces < 1) pieces = 1;
+  }
+  double* logK = reinterpret_cast<double*>(ws.base + (pieces > 1 ? cis::kQueueOff : ws.L.logK));
+  cis::SeqSumArgs sa{lp, lq, mask, ids, offsets, logK, T, n_seq, (int32_t)V, (int32_t)pieces};
+  pa->logK = logK;
+  pa->pieces = (int32_t)pieces;
+  if (avg <= kSeqWaveLen)
+    return launch(cis::seq_sum_kernel(64), (int)((n_seq + 3) / 4), 256, &sa, stream);
+  return launch(cis::seq_sum_kernel(cis::kSeqBlock), (int)(n_seq * pieces), cis::kSeqBlock, &sa,
                 stream);
 }
 
@@ -184,18 +198,17 @@ int64_t seq_count(const LossCall& c) { return c.ext && is_seq_op(c.prm.op) ? c.n
 // before any logits row is read.
 int launch_prepass(const LossCall& c, const Ws& ws, const DeviceInfo& info, hipStream_t stream) {
   const int64_t n_seq = seq_count(c);
+  cis::PrepassArgs pa{};
   if (n_seq > 0) {
     if (int rc = launch_seq_sum(c.logp_old, c.logp_infer, c.mask, c.ids, c.V, c.offsets, n_seq,
-                                c.T, ws, stream))
+                                c.T, ws, &pa, stream))
       return rc;
   }
-  cis::PrepassArgs pa{};
   pa.logp_p = c.logp_old;
   pa.logp_q = c.logp_infer;
   pa.mask = c.mask;
   pa.ids = c.ids;
   pa.offsets = c.offsets;
-  pa.logK = reinterpret_cast<const double*>(ws.base + ws.L.logK);
   pa.ops = op_args(c.prm);
   pa.T = c.T;
   pa.n_seq = n_seq;
@@ -730,17 +743,16 @@ int cis_weights_ex(const float* logp_p, const float* logp_q, const uint8_t* mask
   if (dev < 0) return dev;
   const Ws ws{static_cast<char*>(workspace), L};
   if (T > 0) {
+    cis::PrepassArgs pa{};
     if (seq) {
       if (int rc = launch_seq_sum(logp_p, logp_q, mask, nullptr, 1, seq_offsets, n_seq, T, ws,
-                                  stream))
+                                  &pa, stream))
         return rc;
     }
-    cis::PrepassArgs pa{};
     pa.logp_p = logp_p;
     pa.logp_q = logp_q;
     pa.mask = mask;
     pa.offsets = seq_offsets;
-    pa.logK = reinterpret_cast<const double*>(ws.base + L.logK);
     pa.ops = op_args(*params);
     pa.T = T;
     pa.n_seq = seq ? n_seq : 0;

@@ -11,7 +11,8 @@ namespace cis {
 
 // Workspace layout (bytes), every array 256-byte aligned:
 //   [0, 256)     cis_stats_t
-//   [256, 1280)  the fused pass's row-queue counters, one per 128-byte line
+//   [256, 1280)  the fused pass's row-queue counters, one per 128-byte line; before the rows,
+//                the pieces of the responses' log K, where there are several (kSeqPieceSums)
 //   terms  float[T]   per-row loss term
 //   logk   float[T]   per-row log k (diagnostics)
 //   excess float[T]   per-row k - w (diagnostics)
@@ -34,6 +35,8 @@ constexpr int kRowQueues = 8;
 constexpr size_t kQueueOff = kStatsBytes;
 constexpr size_t kQueueStride = 128;
 constexpr size_t kHeadBytes = kQueueOff + kRowQueues * kQueueStride;
+// Sums of pieces of responses that fit the counters' block (which is cleared after their use).
+constexpr int kSeqPieceSums = (int)((kHeadBytes - kQueueOff) / sizeof(double));
 // Segments per row at most in the split forward pass (the partials per row in the workspace).
 constexpr int kSegMax = 32;
 
@@ -240,9 +243,10 @@ struct SeqSumArgs {
   const uint8_t* mask;      // nullable
   const int64_t* ids;       // nullable (weights path: validity is the mask alone)
   const int64_t* offsets;   // [n_seq + 1]
-  double* logK;             // [n_seq]
+  double* logK;             // [n_seq * pieces]
   int64_t T, n_seq;
   int32_t V;
+  int32_t pieces;           // parts of a response that are summed apart
 };
 
 // Per-token weights of an operator from recorded log-probabilities: the decoupled path's
@@ -253,7 +257,8 @@ struct PrepassArgs {
   const uint8_t* mask;      // nullable
   const int64_t* ids;       // nullable
   const int64_t* offsets;   // sequence operators
-  const double* logK;       // sequence operators
+  const double* logK;       // sequence operators: [n_seq * pieces]
+  int32_t pieces;           // parts of a response's log K, added in order
   OpArgs ops;
   int64_t T, n_seq;
   int32_t V;
@@ -285,10 +290,10 @@ const RowVariant& select_row_variant_ext(int dtype, bool bwd, int32_t nvec);
 const void* finalize_kernel();
 const void* queue_reset_kernel();
 const void* weights_kernel();
-const void* seq_sum_kernel();
+const void* seq_sum_kernel(int threads);  // 64 (a wave per response) or kSeqBlock
 const void* prepass_kernel();
 constexpr int kFinalizeBlock = 1024;
 constexpr int kWeightsBlock = 256;
-constexpr int kSeqBlock = 256;      // four responses per workgroup, one per wave
+constexpr int kSeqBlock = 1024;     // threads of a piece of a long response
 
 }  // namespace cis

@@ -218,3 +218,34 @@ def test_decoupled_full_size_moe_rollout():
 def sample_rows(T, n, seed):
     g = np.random.default_rng(seed)
     return np.unique(np.concatenate([[0, T - 1], g.choice(T, size=n, replace=False)]))
+
+
+@pytest.mark.parametrize("lens", [
+    [512] * 7, [513] * 7,                       # a wave / a workgroup per response
+    [70001],                                    # one response in 34 pieces
+    [1, 0, 90000, 3, 40000],                    # pieces: short, empty and uneven responses
+    [2047] * 129, [2048 * 2 + 1] * 128,         # more responses than piece sums; one piece each
+], ids=["wave", "workgroup", "one_long", "uneven", "many", "full_head"])
+def test_weights_ex_response_lengths(lens):
+    """Seq-TIS over every way a response's log K is summed, with tokens before the first response
+    and after the last: the weight against the oracle's float64 sums (k = K here, |log k| up to
+    about 0.02 per token, so 1e-5 relative plus the float64 summation order)."""
+    n = sum(lens) + 40
+    offs = np.cumsum([30] + lens).astype(np.int64)
+    g = np.random.default_rng(len(lens))
+    lp = np.log(g.uniform(0.2, 0.9, size=n)).astype(np.float32)
+    lq = (lp - g.normal(0, 0.005, size=n)).astype(np.float32)
+    mask = (g.random(n) < 0.9).astype(np.uint8)
+    prm_dev, prm_ref = make_params(X.OP_SEQ_TIS, dict(hi=2.0), 1.0)
+    t = lambda a: torch.from_numpy(np.ascontiguousarray(a)).to(DEV)
+    out = cis.weights_ex(t(lp), t(lq), t(mask), params=prm_dev, seq_offsets=t(offs))
+    torch.cuda.synchronize()
+    inside = slice(30, n - 10)
+    wr, ar = np.zeros(n), np.zeros(n, dtype=bool)
+    wr[inside], ar[inside], logK = X.seq_weights(
+        X.OP_SEQ_TIS, lp.astype(np.float64)[inside] - lq.astype(np.float64)[inside],
+        mask.astype(bool)[inside], offs - 30, prm_ref)
+    assert np.all(np.abs(logK - math.log(2.0)) > 1e-9)   # no response at the cap
+    w = out["w"].cpu().double().numpy()
+    assert np.all(np.abs(w - wr) <= 1e-5 * np.abs(wr) + P.F32_TINY), np.abs(w - wr).max()
+    assert np.array_equal(out["acted"].cpu().numpy().astype(bool), ar)
