@@ -122,11 +122,15 @@ struct Ws {
   cis_stats_t* stats() const { return reinterpret_cast<cis_stats_t*>(base); }
 };
 
-int launch_grid_stride(const void* fn, int64_t T, int block, const DeviceInfo& info, void* arg,
-                       hipStream_t stream) {
+int grid_stride_blocks(int64_t T, int block, const DeviceInfo& info) {
   const int64_t need = (T + block - 1) / block;
   const int64_t cap = (int64_t)info.num_cu * 8;
-  return launch(fn, (int)(need < cap ? need : cap), block, arg, stream);
+  return (int)(need < cap ? need : cap);
+}
+
+int launch_grid_stride(const void* fn, int64_t T, int block, const DeviceInfo& info, void* arg,
+                       hipStream_t stream) {
+  return launch(fn, grid_stride_blocks(T, block, info), block, arg, stream);
 }
 
 // Sequence operators: per-response log K for the pre-pass `pa`, and the kernel that sums it. A
@@ -320,11 +324,24 @@ int launch_rows(const LossCall& c, const Ws& ws, const void* logits, void* dlogi
   return launch(var.fn, grid, var.block, &ra, stream);
 }
 
+// The call's statistics and loss. Few rows by one workgroup; more by one per part and another
+// over the parts (at wpre, which nothing reads after the rows).
 int launch_finalize(const Ws& ws, int64_t T, float* loss_out, hipStream_t stream,
                     cis_stats_t* stats_out = nullptr) {
   cis::FinalizeArgs fa{ws.f(ws.L.terms), ws.b(ws.L.flags), ws.f(ws.L.logk), ws.f(ws.L.excess), T,
-                       ws.stats(), loss_out, stats_out};
-  return launch(cis::finalize_kernel(), 1, cis::kFinalizeBlock, &fa, stream);
+                       ws.stats(), loss_out, stats_out,
+                       reinterpret_cast<cis::RowStats*>(ws.base + ws.L.wpre), 0, 0};
+  if (T <= cis::kFinalizeOne) {
+    const int block = T <= cis::kFinalizeSmall ? 256 : cis::kFinalizeBlock;
+    return launch(cis::finalize_kernel(block, false), 1, block, &fa, stream);
+  }
+  const int64_t even = (T + cis::kFinalizeParts - 1) / cis::kFinalizeParts;
+  fa.rows = even <= cis::kFinalizeRows ? cis::kFinalizeRows : (even + 3) / 4 * 4;
+  fa.nparts = (int32_t)((T + fa.rows - 1) / fa.rows);
+  static_assert(sizeof(cis::RowStats) <= 4 * cis::kFinalizeRows, "the parts fit wpre");
+  if (int rc = launch(cis::finalize_kernel(256, true), fa.nparts, 256, &fa, stream))
+    return rc;
+  return launch(cis::finalize_parts_kernel(), 1, cis::kFinalizeParts, &fa, stream);
 }
 
 int run_loss(const LossCall& c, hipStream_t stream) {
@@ -742,6 +759,12 @@ int cis_weights_ex(const float* logp_p, const float* logp_q, const uint8_t* mask
   const int dev = current_device(&info);
   if (dev < 0) return dev;
   const Ws ws{static_cast<char*>(workspace), L};
+  // each of the pre-pass's workgroups leaves its tokens' statistics, at terms (no more than one
+  // per kWeightsBlock tokens)
+  static_assert(sizeof(cis::RowStats) <= 256, "a workgroup's sums fit its tokens' terms");
+  cis::FinalizeArgs fa{};
+  fa.stats = ws.stats();
+  fa.parts = reinterpret_cast<cis::RowStats*>(ws.base + L.terms);
   if (T > 0) {
     cis::PrepassArgs pa{};
     if (seq) {
@@ -760,17 +783,12 @@ int cis_weights_ex(const float* logp_p, const float* logp_q, const uint8_t* mask
     pa.w_out = w_out;
     pa.acted_out = acted_out;
     pa.eps_out = eps_out;
-    pa.logk_ws = ws.f(L.logk);
-    pa.excess_ws = ws.f(L.excess);
-    pa.flags_ws = ws.b(L.flags);
-    pa.terms_ws = ws.f(L.terms);
-    if (int rc = launch_grid_stride(cis::prepass_kernel(), T, cis::kWeightsBlock, info, &pa,
-                                    stream))
+    pa.parts = fa.parts;
+    fa.nparts = grid_stride_blocks(T, cis::kWeightsBlock, info);
+    if (int rc = launch(cis::prepass_kernel(), fa.nparts, cis::kWeightsBlock, &pa, stream))
       return rc;
   }
-  cis::FinalizeArgs fa{ws.f(L.terms), ws.b(L.flags), ws.f(L.logk), ws.f(L.excess), T,
-                       ws.stats(), nullptr};
-  return launch(cis::finalize_kernel(), 1, cis::kFinalizeBlock, &fa, stream);
+  return launch(cis::finalize_parts_kernel(), 1, cis::kFinalizeParts, &fa, stream);
 }
 
 int cis_loss_fwd(const void* logits, int dtype, int64_t T, int64_t V, int64_t ld,

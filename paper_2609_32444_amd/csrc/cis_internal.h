@@ -16,7 +16,9 @@ namespace cis {
 //   terms  float[T]   per-row loss term
 //   logk   float[T]   per-row log k (diagnostics)
 //   excess float[T]   per-row k - w (diagnostics)
-//   wpre   float[T]   weight from the pre-pass (decoupled path)
+//   wpre   float[T]   weight from the pre-pass (decoupled path); after the rows, the sums of the
+//                     statistics' parts (RowStats) where there are several. cis_weights_ex keeps
+//                     its workgroups' sums at terms instead, and none of the rows' values.
 //   flags  uint8[T]   per-row status bits (kFlag*)
 //   pflags uint8[T]   pre-pass bits (kFlagTrunc = acted on)
 //   logK   double[n_seq]  per-response log K (sequence operators)
@@ -215,6 +217,13 @@ const SegVariant* select_seg_variant(int dtype, int32_t nvec);
 const void* combine_kernel(bool ext, bool lane);
 const void* combine_kernel_ext(bool lane);
 
+// Sums of the statistics over some rows (cis_stats.h).
+struct alignas(64) RowStats {
+  double loss, excess;
+  float max_logk;
+  long long valid, bad_id, nonfinite, acted;
+};
+
 struct FinalizeArgs {
   const float* terms_ws;
   const uint8_t* flags_ws;
@@ -224,7 +233,16 @@ struct FinalizeArgs {
   cis_stats_t* stats;
   float* loss_out;          // nullable
   cis_stats_t* stats_copy;  // nullable: a second copy of the statistics (caller's memory)
+  RowStats* parts;          // sums of the rows' parts, where they are summed apart
+  int64_t rows;             // rows per part
+  int32_t nparts;
 };
+// Rows that one workgroup of 256, or of kFinalizeBlock, sums at once; more are summed in parts of
+// at least kFinalizeRows rows, at most kFinalizeParts of them.
+constexpr int64_t kFinalizeSmall = 1024;
+constexpr int64_t kFinalizeOne = 16384;
+constexpr int64_t kFinalizeRows = 4096;
+constexpr int kFinalizeParts = 256;
 
 struct WeightsArgs {
   const float* logp_train;
@@ -267,10 +285,9 @@ struct PrepassArgs {
   float* eps_out;           // nullable
   float* wpre_ws;           // nullable (loss path)
   uint8_t* pflags_ws;       // nullable (loss path)
-  float* logk_ws;
+  float* logk_ws;           // nullable (loss path), as excess_ws
   float* excess_ws;
-  uint8_t* flags_ws;        // nullable: weights path writes valid/acted bits here
-  float* terms_ws;          // nullable: weights path writes zeros here
+  RowStats* parts;          // nullable: weights path: each workgroup's statistics
 };
 
 // A compiled row-kernel variant: BLOCK threads per workgroup, NV register-resident 16-byte
@@ -287,7 +304,9 @@ struct RowVariant {
 const RowVariant& select_row_variant(int dtype, bool bwd, int32_t nvec);
 const RowVariant& select_row_variant_ext(int dtype, bool bwd, int32_t nvec);
 
-const void* finalize_kernel();
+// 256 or kFinalizeBlock threads; 256 with parts
+const void* finalize_kernel(int block, bool parts);
+const void* finalize_parts_kernel();                 // kFinalizeParts threads
 const void* queue_reset_kernel();
 const void* weights_kernel();
 const void* seq_sum_kernel(int threads);  // 64 (a wave per response) or kSeqBlock

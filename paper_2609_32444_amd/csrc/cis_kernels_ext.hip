@@ -5,6 +5,7 @@
 #define CIS_EXT true
 #include "cis_row.h"
 #include "cis_seg.h"
+#include "cis_stats.h"
 
 namespace cis {
 
@@ -120,12 +121,14 @@ __device__ __forceinline__ float seq_weight(const PrepassArgs& a, int64_t s, boo
 // kernel with l_p = l_old; cis_weights_ex runs it on its own. A workgroup takes 256 consecutive
 // tokens at a time: the responses of the first and the last bound the tokens' searches, and
 // where they are no more than the threads, each response's weight (float64 logarithms and
-// exponential) is formed once and read from LDS.
+// exponential) is formed once and read from LDS. cis_weights_ex's statistics are summed here too
+// (written per token and read again by one workgroup they took 98 us for 524288 tokens).
 // ------------------------------------------------------------------------------------------
 __global__ __launch_bounds__(kWeightsBlock) void cis_prepass_kernel(const PrepassArgs a) {
   __shared__ float sh_w[kWeightsBlock];
   __shared__ bool sh_acted[kWeightsBlock];
   const bool seq = a.ops.op == CIS_OP_SEQ_TIS || a.ops.op == CIS_OP_SEQ_MIS;
+  RowStats st{};
   for (int64_t t0 = (int64_t)blockIdx.x * kWeightsBlock; t0 < a.T;
        t0 += (int64_t)gridDim.x * kWeightsBlock) {
     const int64_t t = t0 + threadIdx.x;
@@ -171,11 +174,14 @@ __global__ __launch_bounds__(kWeightsBlock) void cis_prepass_kernel(const Prepas
     if (a.eps_out) a.eps_out[t] = eps;
     if (a.wpre_ws) a.wpre_ws[t] = w;
     if (a.pflags_ws) a.pflags_ws[t] = acted ? kFlagTrunc : 0;
-    a.logk_ws[t] = logk;
-    a.excess_ws[t] = excess;
-    if (a.flags_ws) a.flags_ws[t] = valid ? (uint8_t)(kFlagValid | (acted ? kFlagTrunc : 0)) : 0;
-    if (a.terms_ws) a.terms_ws[t] = 0.f;
+    if (a.logk_ws) a.logk_ws[t] = logk;
+    if (a.excess_ws) a.excess_ws[t] = excess;
+    if (a.parts)
+      take_row(st, 0.f, valid ? (uint8_t)(kFlagValid | (acted ? kFlagTrunc : 0)) : 0, logk, excess);
   }
+  if (!a.parts) return;  // the loss path's statistics follow the rows
+  st = block_stats<kWeightsBlock>(st);
+  if (threadIdx.x == 0) a.parts[blockIdx.x] = st;
 }
 
 const void* seq_sum_kernel(int threads) {
