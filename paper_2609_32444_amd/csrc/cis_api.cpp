@@ -315,7 +315,10 @@ int launch_rows(const LossCall& c, const Ws& ws, const void* logits, void* dlogi
   const int per_cu = blocks_per_cu(var.fn, var.block, dev);
   const int64_t resident = (int64_t)per_cu * info.num_cu;
   const int grid = (int)(rows < resident ? rows : resident);
-  if (c.bwd) {  // the fused pass takes its rows from a queue (see cis_row_kernel)
+  // the fused pass takes its rows from a queue, except one-wave rows and a workgroup's first
+  // three (see cis_row_kernel)
+  if (!c.bwd || var.block <= 64 || rows <= 3 * (int64_t)grid) ra.queue = nullptr;
+  if (ra.queue) {
     void* qargs[] = {&ra.queue};
     if (hipLaunchKernel(cis::queue_reset_kernel(), dim3(1), dim3(64), qargs, 0, stream) !=
         hipSuccess)

@@ -186,10 +186,10 @@ struct RowArgs {
   const uint8_t* pflags_ws; // pre-pass acted bits[T]
   float* eps_out;           // nullable; rate-1 path only (the pre-pass writes it otherwise)
   float clip_low, clip_high;
-  // row queue of the row kernel (up to kRowQueues counters, kQueueStride bytes apart): a
-  // workgroup's first two rows are blockIdx.x and blockIdx.x + gridDim.x; with n counters in
-  // use (kRowQueues for blocks of up to 512 threads, else 1), counter c hands out the later rows
-  // 2*gridDim.x + c + n*q, q = 0, 1, ... Cleared by queue_reset_kernel before every launch.
+  // row queue of the row kernel (up to kRowQueues counters, kQueueStride bytes apart), or null
+  // where no row comes from it: a workgroup's first three rows are fixed; with n counters in use
+  // (see cis_row_kernel), counter c hands out the later rows 3*gridDim.x + c + n*q, q = 0, 1,
+  // ... Cleared by queue_reset_kernel before every launch.
   unsigned long long* queue;
 };
 

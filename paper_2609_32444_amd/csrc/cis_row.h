@@ -1,6 +1,6 @@
 // Row kernel of the CIS token loss (gfx950), shared by the base and the extended kernels.
-// Row kernel design (one persistent workgroup per row at a time; the fused pass takes its rows
-// from a queue):
+// Row kernel design (one persistent workgroup per row at a time; the fused pass takes rows of more
+// than one wave from a queue):
 //   * Each thread owns the 16-byte vectors v = tid, tid + BLOCK, ... of the row. The first
 //     NV of them stay in VGPRs from the load to the gradient store, so a row that fits in
 //     NV*BLOCK vectors is read from HBM exactly once. Long rows park the next NL slots in
@@ -740,9 +740,9 @@ __global__ __launch_bounds__(BLOCK) void cis_row_kernel(const RowArgs a) {
   }
 
   RowScalars cur = fetch_row_scalars<EXT>(a, blockIdx.x);
-  // The fused pass takes rows from a queue, so that workgroups that meet cheap rows (masked
-  // ones) or run on a faster part of the chip take more of them: the first three rows of a
-  // workgroup are fixed, every later one is drawn as a ticket at the start of the gradient
+  // Fused rows of more than one wave come from a queue, so that workgroups that meet cheap rows
+  // (masked ones) or run on a faster part of the chip take more of them: the first three rows of
+  // a workgroup are fixed, every later one is drawn as a ticket at the start of the gradient
   // sweep two rows before its use and turned into a row at the next row's reduction (the next
   // row is needed at the top of a row, for its scalars and, with PF, its loads). gfx9 counts
   // loads, stores and atomics in one in-order vmcnt, so waiting for a ticket also waits for
@@ -752,11 +752,25 @@ __global__ __launch_bounds__(BLOCK) void cis_row_kernel(const RowArgs a) {
   // kRowQueues counters on separate cache lines, since one counter serialises every draw;
   // counter c hands out the rows congruent to c modulo kRowQueues in increasing order,
   // workgroup b starts on counter b mod kRowQueues and, once its counter has run dry, moves on
-  // to the next. Longer rows draw from one counter (eight measured 0.5-3.5% slower there). The
-  // forward pass keeps the fixed stride: its long rows go to the split kernels, whose
-  // short-lived workgroups balance by themselves.
-  constexpr bool kQueue = BWD;
-  int64_t nrow = (int64_t)blockIdx.x + gridDim.x;
+  // to the next. Longer rows draw from one counter (eight measured 0.5-3.5% slower there).
+  // Without a queue (null: no workgroup has a fourth row) nothing is drawn.
+  //
+  // One-wave rows (up to 1024 vectors) draw too fast for any counters: 16384 rows of 128 to 512
+  // vectors took 141-147 us with the queue and 30-56 us without. They take fixed rows: one of
+  // every gridDim.x, moved on by kRowShift workgroups from round to round, so that a workgroup
+  // does not meet the same place of every response (the padding of a batch is periodic). The
+  // forward pass, whose long rows go to the split kernels, takes every gridDim.x-th row.
+  constexpr bool kQueue = BWD && BLOCK > 64;
+  constexpr bool kShift = BWD && !kQueue;
+  constexpr uint32_t kRowShift = 61;   // (a smaller grid has one round only)
+  uint32_t place = blockIdx.x;         // within the round that nrow is in
+  auto next_place = [&]() {
+    if (!kShift || gridDim.x <= kRowShift) return;
+    place += kRowShift;
+    if (place >= gridDim.x) place -= gridDim.x;
+  };
+  next_place();
+  int64_t nrow = (int64_t)gridDim.x + place;
   bool first = true;             // the first row publishes the workgroup's third, fixed row
   unsigned long long tk = 0ull;  // thread 0's ticket, drawn in the previous row's gradient sweep
   constexpr uint32_t qshift = (BLOCK <= 512 || NV <= 3) ? 3 : 0;
@@ -966,7 +980,8 @@ __global__ __launch_bounds__(BLOCK) void cis_row_kernel(const RowArgs a) {
     uint64_t nq = 0;
     if (kQueue && tid == 0) {
       int64_t r = (int64_t)blockIdx.x + 2 * (int64_t)gridDim.x;
-      if (!first) {
+      if (!first && !a.queue) r = a.T;
+      if (!first && a.queue) {
         asm volatile("" : "+v"(tk));  // keeps the arithmetic on the ticket (and its wait) here
         r = ticket_row(tk, qc);
         for (uint64_t k = 1; k <= qmask && r >= a.T; ++k) {
@@ -978,7 +993,12 @@ __global__ __launch_bounds__(BLOCK) void cis_row_kernel(const RowArgs a) {
       if (NW > 1) sh_q[buf] = nq;
     }
     auto drawn = [&]() -> int64_t {
-      if (!kQueue) return nrow + gridDim.x;
+      if (!kQueue && !kShift) return nrow + gridDim.x;
+      if (kShift) {
+        const int64_t round = nrow - place;
+        next_place();
+        return round + gridDim.x + place;
+      }
       if (NW > 1) return (int64_t)sh_q[buf];
       const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)nq);
       const uint32_t hi = __builtin_amdgcn_readfirstlane((uint32_t)(nq >> 32));
@@ -1043,7 +1063,7 @@ __global__ __launch_bounds__(BLOCK) void cis_row_kernel(const RowArgs a) {
     // the previous row's stores).
     if (BWD) {
       // the ticket of the row after next, drawn ahead of this row's stores
-      if (kQueue && tid == 0) tk = draw(qc);
+      if (kQueue && a.queue && tid == 0) tk = draw(qc);
       slot_fence();
       const uint32_t sgn = coef > 0.f ? GO::kSign : 0u;
       if (valid) {

@@ -95,6 +95,15 @@ def test_row_queue_and_stale_workspace(V, T):
     assert torch.equal(out2["terms"], t1)
 
 
+# Calls that take no row from a queue (up to three per workgroup) and the first that does, with
+# eight and with one counter; and row counts about the steps of the statistics reduction (one
+# workgroup of 256 threads up to 1024 rows, one of 1024 up to 16384, then parts of 4096 rows).
+@pytest.mark.parametrize("V,T", [(151936, 768), (151936, 769), (32768, 1536), (32768, 1545),
+                                 (40, 1024), (40, 1025), (40, 16384), (40, 16385), (40, 40963)])
+def test_fixed_rows_and_statistics_parts(V, T):
+    test_row_queue_and_stale_workspace(V, T)
+
+
 # Forward pass: rows of fewer than 2048 16-byte vectors go through the row kernel (capacities
 # 128, 256, 512, 1024, 2048 vectors); rows of 2048 up to 131072 vectors through the split
 # kernels (segments of 1024, 2048 or 4096 vectors, at most 32 per row); longer rows through the
