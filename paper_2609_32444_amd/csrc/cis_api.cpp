@@ -486,7 +486,7 @@ int run_lmhead(const LmHeadCall& m, hipStream_t stream) {
   __bf16* Ht = reinterpret_cast<__bf16*>(base + LM.ht);
   __bf16* Gb = reinterpret_cast<__bf16*>(base + LM.gb);
   float* part = reinterpret_cast<float*>(base + LM.part);
-  int* queue = reinterpret_cast<int*>(base + LM.queue);
+  cis::GemmQueuePool queues{reinterpret_cast<int*>(base + LM.queue)};
   auto ok = [](hipError_t e) { return e == hipSuccess ? CIS_OK : CIS_ERR_LAUNCH; };
   const __bf16* hid = static_cast<const __bf16*>(m.hidden);
   const int ncu = info.num_cu;
@@ -518,7 +518,7 @@ int run_lmhead(const LmHeadCall& m, hipStream_t stream) {
     ga.e.part = reinterpret_cast<float2*>(base + LM.tpart);
     ga.e.ldp = LM.ntv;
     ga.e.zy = reinterpret_cast<float*>(base + LM.tzy);
-    if (int rc = ok(cis::launch_gemm_epi(ga, queue, ncu, stream))) return rc;
+    if (int rc = ok(cis::launch_gemm_epi(ga, queues, ncu, stream))) return rc;
     cis::RowArgs ra = row_args(c, ws, nullptr, nullptr, 0, 0, t0, tc);
     cis::SegArgs sa{};
     sa.part = ga.e.part;
@@ -533,7 +533,7 @@ int run_lmhead(const LmHeadCall& m, hipStream_t stream) {
       ga.e.gp = sa.gp;
       ga.e.G = Gb;
       ga.e.ldg = LM.ldv;
-      if (int rc = ok(cis::launch_gemm_epi(ga, queue, ncu, stream))) return rc;
+      if (int rc = ok(cis::launch_gemm_epi(ga, queues, ncu, stream))) return rc;
       // G^T (operand of dL/dW) into the group's columns t0 - g0 ..
       if (int rc = ok(cis::launch_transpose(
               cis::TransposeArgs{Gb, Gt + (t0 - g0), nullptr, tc, V, LM.ldv, LM.ldc, 0, nullptr},
@@ -555,19 +555,19 @@ int run_lmhead(const LmHeadCall& m, hipStream_t stream) {
     // dL/dh_c = G W = G (W^T)^T
     if (int rc = ok(cis::launch_gemm_nt(
             cis::gemm_args(Gb, Wt, m.dhidden + t0 * m.ld_dh, tc, H, V, LM.ldv, LM.ldv, m.ld_dh),
-            false, part, queue, ncu, stream)))
+            false, part, LM.splits, queues, ncu, stream)))
       return rc;
     // dL/dW (+)= G^T h over the group's rows, once its last chunk is in
     const int64_t gend = g0 + group < T ? g0 + group : T;
     if (t0 + tc < gend) continue;
     if (int rc = ok(cis::launch_gemm_nt(
             cis::gemm_args(Gt, Ht, m.dweight, V, H, gend - g0, LM.ldc, LM.ldc, m.ld_dw),
-            m.accumulate || g0 > 0, nullptr, queue, ncu, stream)))
+            m.accumulate || g0 > 0, nullptr, 1, queues, ncu, stream)))
       return rc;
   }
   if (bwd && T == 0 && !m.accumulate) {  // no rows: dL/dW = 0 (an empty contraction)
     if (int rc = ok(cis::launch_gemm_nt(
-            cis::gemm_args(Wt, Wt, m.dweight, V, H, 0, 8, 8, m.ld_dw), false, nullptr, queue,
+            cis::gemm_args(Wt, Wt, m.dweight, V, H, 0, 8, 8, m.ld_dw), false, nullptr, 1, queues,
             ncu, stream)))
       return rc;
   }

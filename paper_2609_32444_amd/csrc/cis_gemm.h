@@ -80,26 +80,32 @@ constexpr int kGemmTile = 256;      // C tile per workgroup (rows and columns)
 constexpr int kGemmBK = 64;         // contraction slab
 constexpr int kGemmWaveM = 128;     // C tile per wave: 128 rows x 64 columns (8 waves)
 constexpr int kGemmWaveN = 64;
-constexpr int kGemmMaxSplits = 8;   // split-K partial buffers
 constexpr int kTransposeTile = 64;
 constexpr int kGemmQueues = 8;      // one work queue per XCD
 
-// Number of K splits launch_gemm_nt uses for an M x N x K product when given a partial buffer
-// (enough workgroups for every CU; 1 when the tiles already cover the chip).
-int64_t gemm_splitk_count(int64_t M, int64_t N, int64_t K, int num_cu);
+// Device scratch for the products' work queues, one set of kGemmQueues counters per product. A
+// kernel clears all the sets before the first is used and again when they are used up (one
+// launch per kSets products rather than one each: about 5 us of every product's time).
+struct GemmQueuePool {
+  static constexpr int kSets = 8;
+  int* base;                // kSets * kGemmQueues ints
+  int used = kSets;
+  hipError_t take(int** queue, hipStream_t stream);
+};
+
+// Number of K splits, up to max_splits, that launch_gemm_nt uses for an M x N x K product.
+int64_t gemm_splitk_count(int64_t M, int64_t N, int64_t K, int64_t max_splits, int num_cu);
 
 // Launch on `stream`; `beta` adds the product to C instead of overwriting it. With `partial`
-// (float32, >= gemm_splitk_count(...) * M * N elements, 16-byte aligned) small products are
-// split along K and the partials summed in a fixed order. With `queue` (kGemmQueues ints of
-// device scratch, cleared on `stream` before the product) and more tiles than CUs, one
-// workgroup per CU takes tiles from per-XCD queues until all are taken, so XCDs that run faster
+// (float32, max_splits * M * N elements, 16-byte aligned) small products are split along K and
+// the partials summed in a fixed order. With more tiles than CUs, one workgroup per CU takes tiles from per-XCD queues until all are taken, so XCDs that run faster
 // take over tiles of slower ones. Results do not depend on it: a tile is computed the same way
 // by whichever workgroup takes it.
-hipError_t launch_gemm_nt(GemmArgs g, bool beta, float* partial, int* queue, int num_cu,
-                          hipStream_t stream);
+hipError_t launch_gemm_nt(GemmArgs g, bool beta, float* partial, int64_t max_splits,
+                          GemmQueuePool& queues, int num_cu, hipStream_t stream);
 // The logits product of a row chunk with a row-loss epilogue (kEpiLse, kEpiGrad or
 // kEpiLseStore; no split-K; C only with kEpiLseStore): M rows of h, N = V columns of W.
-hipError_t launch_gemm_epi(GemmArgs g, int* queue, int num_cu, hipStream_t stream);
+hipError_t launch_gemm_epi(GemmArgs g, GemmQueuePool& queues, int num_cu, hipStream_t stream);
 hipError_t launch_transpose(TransposeArgs t, bool in_f32, hipStream_t stream);
 
 }  // namespace cis

@@ -22,6 +22,7 @@
 // The B fragment is passed as the first operand, so a lane's four registers hold four
 // consecutive columns of one row of C and the epilogue stores 16 bytes at a time.
 #include <hip/hip_runtime.h>
+#include <math.h>
 #include <stdint.h>
 
 #include "cis_gemm.h"
@@ -545,14 +546,22 @@ struct ReduceArgs {
   bool beta;
 };
 
+// Four elements per thread (VEC: rows of 16-byte vectors), the splits' loads independent.
+template <bool VEC>
 __global__ __launch_bounds__(256) void splitk_reduce_kernel(const ReduceArgs r) {
-  const int64_t total = r.M * r.N;
+  constexpr int E = VEC ? 4 : 1;
+  typedef float vec __attribute__((ext_vector_type(E)));
+  const uint32_t per = (uint32_t)(r.N / E);   // vectors per row
+  const int64_t total = r.M * per;
   for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < total;
        i += (int64_t)gridDim.x * 256) {
-    const int64_t m = i / r.N, n = i % r.N;
-    float s = 0.f;
-    for (int k = 0; k < r.splits; ++k) s += r.P[k * r.split_stride + m * r.N + n];
-    float* c = r.C + m * r.ldc + n;
+    const int64_t m = i / per;
+    const int64_t n = (i - m * per) * E;
+    vec s{};
+#pragma unroll 4
+    for (int k = 0; k < r.splits; ++k)
+      s += *(const vec*)(r.P + k * r.split_stride + m * r.N + n);
+    vec* c = (vec*)(r.C + m * r.ldc + n);
     *c = r.beta ? s * r.alpha + *c : s * r.alpha;
   }
 }
@@ -625,22 +634,20 @@ __global__ __launch_bounds__(256) void transpose_kernel(const TransposeArgs t) {
   }
 }
 
-__global__ __launch_bounds__(kGemmQueues) void zero_queue_kernel(int* q) { q[threadIdx.x] = 0; }
+constexpr int kPoolInts = GemmQueuePool::kSets * kGemmQueues;
+__global__ __launch_bounds__(kPoolInts) void zero_queue_kernel(int* q) { q[threadIdx.x] = 0; }
 
 int64_t gemm_tiles(const GemmArgs& g) {
   return ((g.M + kGemmTile - 1) / kGemmTile) * ((g.N + kGemmTile - 1) / kGemmTile);
 }
 
 // Launches `fn` over g.units units, one workgroup per CU at most (the LDS slabs allow one). With
-// more units than CUs the workgroups take them from the queues, cleared first by a kernel rather
-// than a memset node, so that the call can be graph-captured.
-hipError_t launch_units(GemmArgs g, const void* fn, int* queue, int num_cu, hipStream_t stream) {
-  g.queue = g.units > num_cu ? queue : nullptr;
-  if (g.queue) {
-    void* zargs[] = {&g.queue};
-    if (hipError_t e = hipLaunchKernel((const void*)&zero_queue_kernel, dim3(1),
-                                       dim3(kGemmQueues), zargs, 0, stream))
-      return e;
+// more units than CUs the workgroups take them from queues.
+hipError_t launch_units(GemmArgs g, const void* fn, GemmQueuePool& queues, int num_cu,
+                        hipStream_t stream) {
+  g.queue = nullptr;
+  if (g.units > num_cu) {
+    if (hipError_t e = queues.take(&g.queue, stream)) return e;
   }
   const int64_t grid = g.queue ? num_cu : g.units;
   void* args[] = {&g};
@@ -649,7 +656,20 @@ hipError_t launch_units(GemmArgs g, const void* fn, int* queue, int num_cu, hipS
 
 }  // namespace
 
-hipError_t launch_gemm_epi(GemmArgs g, int* queue, int num_cu, hipStream_t stream) {
+// (A kernel rather than a memset node clears the counters, so that a call can be captured.)
+hipError_t GemmQueuePool::take(int** queue, hipStream_t stream) {
+  if (used == kSets) {
+    void* zargs[] = {&base};
+    if (hipError_t e = hipLaunchKernel((const void*)&zero_queue_kernel, dim3(1), dim3(kPoolInts),
+                                       zargs, 0, stream))
+      return e;
+    used = 0;
+  }
+  *queue = base + kGemmQueues * used++;
+  return hipSuccess;
+}
+
+hipError_t launch_gemm_epi(GemmArgs g, GemmQueuePool& queues, int num_cu, hipStream_t stream) {
   if (g.M <= 0 || g.N <= 0) return hipSuccess;
   g.m_fastest = g.M <= g.N;
   g.k_split = g.K > 0 ? g.K : 1;
@@ -661,23 +681,35 @@ hipError_t launch_gemm_epi(GemmArgs g, int* queue, int num_cu, hipStream_t strea
                    : g.epi == kEpiLseStore ? (const void*)&gemm_bf16_kernel<false, kEpiLseStore>
                                            : nullptr;
   if (!fn) return hipErrorInvalidValue;
-  return launch_units(g, fn, queue, num_cu, stream);
+  return launch_units(g, fn, queues, num_cu, stream);
 }
 
-int64_t gemm_splitk_count(int64_t M, int64_t N, int64_t K, int num_cu) {
+// The number of splits with the shortest estimate: rounds of one unit per CU, each its share of
+// the contraction and kUnitSlabs for its start and epilogue, and the reduction's traffic at
+// 5 TB/s; in slabs of 1.35 us (measured of a full chip). A split keeps kMinSplitSlabs at least.
+// 4096 x 2048 x 151936: 2 splits (1 unit per CU); 1777 x 1600 x 50257: 5 (245 units; 8 splits
+// make 392, a second round half empty).
+int64_t gemm_splitk_count(int64_t M, int64_t N, int64_t K, int64_t max_splits, int num_cu) {
+  constexpr double kUnitSlabs = 6, kMinSplitSlabs = 8, kReduceSlabs = 4 / (5e12 * 1.35e-6);
   const int64_t tiles = ((M + kGemmTile - 1) / kGemmTile) * ((N + kGemmTile - 1) / kGemmTile);
-  int64_t s = 1;
-  // split the contraction until every CU has a tile, keeping >= 2048 of K per split
-  while (s < kGemmMaxSplits && tiles * s < num_cu && K / (2 * s) >= 2048) s *= 2;
-  return s;
+  const double slabs = (double)K / kGemmBK;
+  int64_t best = 1;
+  double best_t = INFINITY;
+  for (int64_t s = 1; s <= max_splits && (s == 1 || slabs / s >= kMinSplitSlabs); ++s) {
+    const double rounds = (double)((tiles * s + num_cu - 1) / num_cu);
+    const double t = rounds * (2 * ceil(slabs / (2 * s)) + kUnitSlabs) +
+                     (s > 1 ? kReduceSlabs * (s + 1) * (double)M * (double)N : 0);
+    if (t < best_t) best_t = t, best = s;
+  }
+  return best;
 }
 
-hipError_t launch_gemm_nt(GemmArgs g, bool beta, float* partial, int* queue, int num_cu,
-                          hipStream_t stream) {
+hipError_t launch_gemm_nt(GemmArgs g, bool beta, float* partial, int64_t max_splits,
+                          GemmQueuePool& queues, int num_cu, hipStream_t stream) {
   if (g.M <= 0 || g.N <= 0) return hipSuccess;
   // A is M x K, B is N x K: the smaller one's tiles run fastest
   g.m_fastest = g.M <= g.N;
-  const int64_t splits = partial ? gemm_splitk_count(g.M, g.N, g.K, num_cu) : 1;
+  const int64_t splits = partial ? gemm_splitk_count(g.M, g.N, g.K, max_splits, num_cu) : 1;
   g.units = gemm_tiles(g) * splits;
   const void* fn = beta && splits <= 1 ? (const void*)&gemm_bf16_kernel<true, kEpiStore>
                                        : (const void*)&gemm_bf16_kernel<false, kEpiStore>;
@@ -686,10 +718,12 @@ hipError_t launch_gemm_nt(GemmArgs g, bool beta, float* partial, int* queue, int
     g.k_split = g.K > 0 ? g.K : 1;
     g.c_split_stride = 0;
     g.c_vec = c_aligned;
-    return launch_units(g, fn, queue, num_cu, stream);
+    return launch_units(g, fn, queues, num_cu, stream);
   }
   // split-K: partial products into `partial` [splits][M][N], then summed in split order
-  const int64_t kper = ((g.K + splits - 1) / splits + kGemmBK - 1) / kGemmBK * kGemmBK;
+  // (whole pairs of slabs: an odd one is multiplied with a slab of zeros)
+  const int64_t kper =
+      ((g.K + splits - 1) / splits + 2 * kGemmBK - 1) / (2 * kGemmBK) * (2 * kGemmBK);
   GemmArgs p = g;
   p.C = partial;
   p.ldc = g.N;
@@ -697,12 +731,14 @@ hipError_t launch_gemm_nt(GemmArgs g, bool beta, float* partial, int* queue, int
   p.k_split = kper;
   p.c_split_stride = g.M * g.N;
   p.c_vec = ((uintptr_t)partial % 16 == 0) && g.N % 4 == 0;
-  if (hipError_t e = launch_units(p, fn, queue, num_cu, stream)) return e;
+  if (hipError_t e = launch_units(p, fn, queues, num_cu, stream)) return e;
   ReduceArgs r{partial, g.C, g.M, g.N, g.ldc, g.M * g.N, (int32_t)splits, g.alpha, beta};
-  const int64_t blocks = (g.M * g.N + 255) / 256;
+  const bool vec = c_aligned && p.c_vec;
+  const int64_t blocks = (g.M * g.N / (vec ? 4 : 1) + 255) / 256;
+  const void* rfn = vec ? (const void*)&splitk_reduce_kernel<true>
+                        : (const void*)&splitk_reduce_kernel<false>;
   void* args[] = {&r};
-  return hipLaunchKernel((const void*)&splitk_reduce_kernel,
-                         dim3((unsigned)(blocks < 4096 ? blocks : 4096)), dim3(256), args, 0,
+  return hipLaunchKernel(rfn, dim3((unsigned)(blocks < 4096 ? blocks : 4096)), dim3(256), args, 0,
                          stream);
 }
 
