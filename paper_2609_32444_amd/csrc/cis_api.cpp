@@ -329,11 +329,15 @@ int launch_rows(const LossCall& c, const Ws& ws, const void* logits, void* dlogi
 
 // The call's statistics and loss. Few rows by one workgroup; more by one per part and another
 // over the parts (at wpre, which nothing reads after the rows).
+cis::FinalizeArgs finalize_args(const Ws& ws, int64_t T, float* loss_out,
+                                cis_stats_t* stats_out) {
+  return cis::FinalizeArgs{ws.f(ws.L.terms), ws.b(ws.L.flags), ws.f(ws.L.logk),
+                           ws.f(ws.L.excess), T, ws.stats(), loss_out, stats_out,
+                           reinterpret_cast<cis::RowStats*>(ws.base + ws.L.wpre), 0, 0};
+}
 int launch_finalize(const Ws& ws, int64_t T, float* loss_out, hipStream_t stream,
                     cis_stats_t* stats_out = nullptr) {
-  cis::FinalizeArgs fa{ws.f(ws.L.terms), ws.b(ws.L.flags), ws.f(ws.L.logk), ws.f(ws.L.excess), T,
-                       ws.stats(), loss_out, stats_out,
-                       reinterpret_cast<cis::RowStats*>(ws.base + ws.L.wpre), 0, 0};
+  cis::FinalizeArgs fa = finalize_args(ws, T, loss_out, stats_out);
   if (T <= cis::kFinalizeOne) {
     const int block = T <= cis::kFinalizeSmall ? 256 : cis::kFinalizeBlock;
     return launch(cis::finalize_kernel(block, false), 1, block, &fa, stream);
@@ -345,6 +349,27 @@ int launch_finalize(const Ws& ws, int64_t T, float* loss_out, hipStream_t stream
   if (int rc = launch(cis::finalize_kernel(256, true), fa.nparts, 256, &fa, stream))
     return rc;
   return launch(cis::finalize_parts_kernel(), 1, cis::kFinalizeParts, &fa, stream);
+}
+
+// The fused pass over few long rows, statistics included (see cis_seg_grad_kernel).
+int launch_seg_grad(const LossCall& c, const Ws& ws, const cis::SegGradVariant& v,
+                    hipStream_t stream) {
+  cis::RowArgs ra = row_args(c, ws, c.logits, c.dlogits, c.ld, c.ld_g, 0, c.T);
+  cis::SegArgs sa{};
+  sa.segvec = v.block * v.k;
+  sa.nseg = (int32_t)((ra.nvec + sa.segvec - 1) / sa.segvec);
+  sa.part = reinterpret_cast<float2*>(ws.base + ws.L.part);
+  sa.zy = ws.f(ws.L.zy);
+  sa.stride = cis::kSegMax;
+  sa.done = reinterpret_cast<uint32_t*>(ws.base + cis::kQueueOff);
+  cis::FinalizeArgs fa = finalize_args(ws, c.T, c.loss_out, c.stats_out);
+  const unsigned grid = (unsigned)(c.T * sa.nseg);
+  void* sargs[] = {&ra, &sa};
+  void* gargs[] = {&ra, &sa, &fa};
+  if (hipLaunchKernel(v.fn, dim3(grid), dim3(v.block), sargs, 0, stream) != hipSuccess ||
+      hipLaunchKernel(v.grad, dim3(grid), dim3(v.block), gargs, 0, stream) != hipSuccess)
+    return CIS_ERR_LAUNCH;
+  return CIS_OK;
 }
 
 int run_loss(const LossCall& c, hipStream_t stream) {
@@ -363,8 +388,15 @@ int run_loss(const LossCall& c, hipStream_t stream) {
   if (n_seq > 0 && T > 0 && !c.offsets) return CIS_ERR_NULL;
   if (!aligned(c.workspace, 256)) return CIS_ERR_ALIGN;
   // the forward pass keeps room for the split kernels' partials (cis_workspace_bytes covers it)
-  const cis::WsLayout L = cis::ws_layout(T, n_seq, !bwd);
+  cis::WsLayout L = cis::ws_layout(T, n_seq, !bwd);
   if (c.workspace_bytes < L.total) return CIS_ERR_WORKSPACE;
+  // so does the fused pass over few long rows, where the workspace has that room
+  cis::SegGradVariant sg;
+  const cis::WsLayout Lseg = cis::ws_layout(T, n_seq, true);
+  const int32_t nvec = (int32_t)((V + 16 / esize - 1) / (16 / esize));
+  const bool few = bwd && T > 0 && c.workspace_bytes >= Lseg.total &&
+                   cis::select_seg_grad_variant(c.dtype, c.ext, T, nvec, &sg);
+  if (few) L = Lseg;
   if (T > 0) {
     if (!aligned(c.logits, 16) || (c.ld * esize) % 16 != 0) return CIS_ERR_ALIGN;
     if (bwd) {
@@ -387,6 +419,7 @@ int run_loss(const LossCall& c, hipStream_t stream) {
     if (c.logp_old) {
       if (int rc = launch_prepass(c, ws, info, stream)) return rc;
     }
+    if (few) return launch_seg_grad(c, ws, sg, stream);
     if (int rc = launch_rows(c, ws, c.logits, c.dlogits, c.ld, c.ld_g, 0, T, dev, info, stream))
       return rc;
   }

@@ -22,10 +22,10 @@ namespace cis {
 //   flags  uint8[T]   per-row status bits (kFlag*)
 //   pflags uint8[T]   pre-pass bits (kFlagTrunc = acted on)
 //   logK   double[n_seq]  per-response log K (sequence operators)
-//   part   float2[T * kSegMax]  per-segment (max, exp-sum) of the split forward pass
-//   zy     float[T]           the sampled logit (split forward pass)
-// The last two exist only in the layout of the forward entry points (`seg`); the fused pass and
-// the LM-head path do not use them.
+//   part   float2[T * kSegMax]  per-segment (max, exp-sum) of the split passes
+//   zy     float[T]           the sampled logit (split passes)
+// The last two exist only in the layout of the forward entry points and of the fused pass over
+// few rows (`seg`); the other fused calls and the LM-head path do not use them.
 constexpr size_t kStatsBytes = 256;
 static_assert(sizeof(cis_stats_t) <= kStatsBytes, "the statistics fit their block");
 // The row queue: up to kRowQueues counters of 8 bytes, each on a 128-byte line of its own.
@@ -214,8 +214,10 @@ struct SegArgs {
   int32_t segvec;   // 16-byte vectors per segment (split forward pass)
   int64_t stride;   // pieces per row in `part`
   GradParams* gp;   // [T] nullable: gradient parameters for the fused LM-head pass
+  uint32_t* done;   // nullable: rows whose outputs are stored (the fused pass over few rows)
 };
 constexpr int kCombineBlock = 256;
+constexpr int kSegGradBlock = 128, kSegGradK = 8;   // 16 KiB of logits per workgroup
 // A compiled segment kernel: `block` threads with K 16-byte vectors each, so block * K vectors
 // per segment.
 struct SegVariant {
@@ -225,6 +227,14 @@ struct SegVariant {
 // The segment kernel for rows of `nvec` vectors, or nullptr when the row kernel serves them
 // better (short rows) or they need more than kSegMax segments of the largest variant.
 const SegVariant* select_seg_variant(int dtype, int32_t nvec);
+// The fused pass over few long rows: cis_seg_kernel, then cis_seg_grad_kernel over the same
+// segments. `fn` is the segment kernel; null when the row kernel serves such a call better.
+struct SegGradVariant {
+  int block, k;
+  const void *fn, *grad;
+};
+bool select_seg_grad_variant(int dtype, bool ext, int64_t T, int32_t nvec, SegGradVariant* v);
+const void* seg_grad_kernel_ext(int dtype);
 // lane: one lane per row (rows of at most kSegMax pieces), else one wave per row
 const void* combine_kernel(bool ext, bool lane);
 const void* combine_kernel_ext(bool lane);

@@ -4,7 +4,6 @@
 #define CIS_EXT false
 #include "cis_row.h"
 #include "cis_seg.h"
-#include "cis_stats.h"
 
 namespace cis {
 
@@ -105,6 +104,29 @@ const SegVariant* select_seg_variant(int dtype, int32_t nvec) {
   for (int i = 0; i < 3; ++i)
     if ((int64_t)t[i].block * t[i].k * kSegMax >= nvec) return &t[i];
   return nullptr;
+}
+
+// Few rows that a compute unit each would work on too long. Fused calls in us, row kernel and
+// split (bf16): V = 50257, 32 rows 12.4 and 11.8, 64 rows 12.9 and 13.6; V = 100003, 128 rows 18.8
+// and 18.2, 192 rows 20.8 and 23.7; V = 151936, 64 rows 21.0 and 15.4, 96 rows 21.1 and 17.9, 128
+// rows 21.6 and 22.6; V = 262144 (LDS slots and streamed ones), 64 rows 35.8 and 17.4, 192 rows
+// 52.6 and 47.2, 256 rows 62.7 and 62.3.
+static int64_t seg_grad_max_rows(int32_t nvec) {
+  return nvec > 19456 ? 192 : (nvec >= 12288 ? 112 : (nvec >= 6144 ? 32 : 0));
+}
+
+bool select_seg_grad_variant(int dtype, bool ext, int64_t T, int32_t nvec, SegGradVariant* v) {
+  constexpr int kVec = kSegGradBlock * kSegGradK;
+  if (T > seg_grad_max_rows(nvec) || nvec > kVec * kSegMax) return false;
+  const bool b = dtype == CIS_BF16;
+  *v = SegGradVariant{
+      kSegGradBlock, kSegGradK,
+      b ? (const void*)&cis_seg_kernel<Bf16, kSegGradBlock, kSegGradK, true, 0>
+        : (const void*)&cis_seg_kernel<F32, kSegGradBlock, kSegGradK, true, 0>,
+      ext ? seg_grad_kernel_ext(dtype)
+      : b ? (const void*)&cis_seg_grad_kernel<Bf16, kSegGradBlock, kSegGradK, false>
+          : (const void*)&cis_seg_grad_kernel<F32, kSegGradBlock, kSegGradK, false>};
+  return true;
 }
 
 const void* combine_kernel(bool ext, bool lane) {

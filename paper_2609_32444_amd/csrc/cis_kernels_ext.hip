@@ -5,7 +5,6 @@
 #define CIS_EXT true
 #include "cis_row.h"
 #include "cis_seg.h"
-#include "cis_stats.h"
 
 namespace cis {
 
@@ -190,6 +189,10 @@ const void* seq_sum_kernel(int threads) {
 }
 const void* combine_kernel_ext(bool lane) {
   return lane ? (const void*)&cis_combine_lane_kernel<true> : (const void*)&cis_combine_kernel<true>;
+}
+const void* seg_grad_kernel_ext(int dtype) {
+  return dtype == CIS_BF16 ? (const void*)&cis_seg_grad_kernel<Bf16, kSegGradBlock, kSegGradK, true>
+                           : (const void*)&cis_seg_grad_kernel<F32, kSegGradBlock, kSegGradK, true>;
 }
 const void* prepass_kernel() { return (const void*)&cis_prepass_kernel; }
 

@@ -562,7 +562,22 @@ __device__ __forceinline__ float displacement(float lp, float lq, float one_m_p)
 struct RowResult {
   float coef, lse, one_m_p;
 };
-template <bool EXT>
+// A store; DEV: one that every compute unit sees once it is complete (it is written through this
+// XCD's L2, as a relaxed store of device scope).
+template <bool DEV, class T>
+__device__ __forceinline__ void put(T* p, T v) {
+  if (DEV)
+    __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  else
+    *p = v;
+}
+template <class T>
+__device__ __forceinline__ T get_dev(const T* p) {
+  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+// COH: the values that the statistics read are stored for the whole device at once, because a
+// workgroup of the same kernel reads them (cis_seg_grad_kernel).
+template <bool EXT, bool COH = false>
 __device__ __forceinline__ RowResult row_epilogue(const RowArgs& a, const RowScalars& rsc,
                                                   int64_t row, float M, float sr, float zy,
                                                   bool writer) {
@@ -615,13 +630,14 @@ __device__ __forceinline__ RowResult row_epilogue(const RowArgs& a, const RowSca
   if (writer) {
     if (a.logp_train_out) a.logp_train_out[row] = ltr;
     if (a.terms_user) a.terms_user[row] = term;
-    a.terms_ws[row] = term;
-    a.flags_ws[row] = kFlagValid | (acted ? kFlagTrunc : 0) | (nonfinite ? kFlagNonFinite : 0);
+    put<COH>(a.terms_ws + row, term);
+    put<COH>(a.flags_ws + row, (uint8_t)(kFlagValid | (acted ? kFlagTrunc : 0) |
+                                         (nonfinite ? kFlagNonFinite : 0)));
     if (!decoupled) {  // the decoupled path's pre-pass wrote these
       if (a.w_out) a.w_out[row] = w;
       if (a.trunc_out) a.trunc_out[row] = acted ? 1 : 0;
-      a.logk_ws[row] = logk;
-      a.excess_ws[row] = excess;
+      put<COH>(a.logk_ws + row, logk);
+      put<COH>(a.excess_ws + row, excess);
       if (EXT && a.eps_out) a.eps_out[row] = eps;
     }
   }
@@ -630,17 +646,17 @@ __device__ __forceinline__ RowResult row_epilogue(const RowArgs& a, const RowSca
 
 // Outputs of an invalid row (masked, or id out of range): zeros, and the bad-id flag for an
 // unmasked row.
-template <bool EXT>
+template <bool EXT, bool COH = false>
 __device__ __forceinline__ void row_invalid(const RowArgs& a, const RowScalars& rsc, int64_t row) {
   if (a.logp_train_out) a.logp_train_out[row] = 0.f;
   if (a.terms_user) a.terms_user[row] = 0.f;
-  a.terms_ws[row] = 0.f;
-  a.flags_ws[row] = rsc.on ? kFlagBadId : 0;
+  put<COH>(a.terms_ws + row, 0.f);
+  put<COH>(a.flags_ws + row, (uint8_t)(rsc.on ? kFlagBadId : 0));
   if (!(EXT && a.logp_old)) {
     if (a.w_out) a.w_out[row] = 0.f;
     if (a.trunc_out) a.trunc_out[row] = 0;
-    a.logk_ws[row] = 0.f;
-    a.excess_ws[row] = 0.f;
+    put<COH>(a.logk_ws + row, 0.f);
+    put<COH>(a.excess_ws + row, 0.f);
     if (EXT && a.eps_out) a.eps_out[row] = 0.f;
   }
 }

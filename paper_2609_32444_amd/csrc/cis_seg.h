@@ -22,13 +22,14 @@
 #pragma once
 
 #include "cis_row.h"
+#include "cis_stats.h"
 
 namespace cis {
 
 // BLOCK threads take a segment of BLOCK * K vectors. RE: re-unpack the vectors for the
 // exp-sum instead of keeping K * EPV floats alive from the max pass (fewer registers, one more
 // VALU operation per logit).
-template <class E, int BLOCK, int K, bool RE>
+template <class E, int BLOCK, int K, bool RE, int AUX = kAuxNT>
 __global__ __launch_bounds__(BLOCK) void cis_seg_kernel(const RowArgs a, const SegArgs g) {
   constexpr int EPV = E::kPerVec;
   constexpr int NW = BLOCK / 64;
@@ -36,6 +37,7 @@ __global__ __launch_bounds__(BLOCK) void cis_seg_kernel(const RowArgs a, const S
   __shared__ float sh_s[NW];
   const int V = a.V;
   const int64_t total = a.T * (int64_t)g.nseg;
+  if (g.done && blockIdx.x == 0 && threadIdx.x == 0) *g.done = 0u;
   for (int64_t b = blockIdx.x; b < total; b += gridDim.x) {
     int tid = threadIdx.x;
     const int64_t row = b / g.nseg;
@@ -49,7 +51,7 @@ __global__ __launch_bounds__(BLOCK) void cis_seg_kernel(const RowArgs a, const S
     u32x4 r[K];
     static_for<K>([&](auto I) {
       constexpr int k = I;
-      r[k] = bload(rs, (uint32_t)(v0 + k * BLOCK) * 16u, 0u);
+      r[k] = bload_aux<AUX>(rs, (uint32_t)(v0 + k * BLOCK) * 16u);
     });
     // vectors that reach past the row (the ragged last one, and whole vectors beyond it in
     // the last segment) read as -inf
@@ -103,6 +105,76 @@ __global__ __launch_bounds__(BLOCK) void cis_seg_kernel(const RowArgs a, const S
     }
     __syncthreads();  // sh_m / sh_s are reused by the next segment of this workgroup
   }
+}
+
+// The gradient of few long rows, after cis_seg_kernel (same segments): a workgroup folds its row's
+// pairs, runs the row's epilogue (each wave redundantly; the first segment's workgroup stores the
+// row's outputs) and writes its segment of the gradient. The workgroup whose row is the last to be
+// stored sums the statistics: rows are counted in g.done, cleared by cis_seg_kernel.
+// With fewer rows than compute units the row kernel leaves most of the chip idle and takes a
+// row's whole latency (96 rows of V = 151936: 19.5 us of 20.8); the segments spread over all of
+// it (8.7 and 10.4 us), and the second read of the logits comes from the caches: cis_seg_kernel
+// reads them with the default policy for that (non-temporal: 19.6 against 17.9 us per call), and
+// both kernels put a segment on the same XCD.
+template <class E, int BLOCK, int K, bool EXT>
+__global__ __launch_bounds__(BLOCK) void cis_seg_grad_kernel(const RowArgs a, const SegArgs g,
+                                                             const FinalizeArgs fa) {
+  constexpr int EPV = E::kPerVec;
+  __shared__ bool sh_last;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int64_t row = blockIdx.x / g.nseg;
+  const int seg = (int)(blockIdx.x - row * g.nseg);
+  const RowScalars rsc = fetch_row_scalars<EXT>(a, row);
+  const bool valid = rsc.valid(a.V), writer = seg == 0 && tid == 0;
+  const bool ragged = a.V % EPV != 0;
+  const __amdgpu_buffer_rsrc_t rs =
+      make_rsrc((const char*)a.logits + row * a.row_bytes, valid ? (uint32_t)a.nvec * 16u : 0u);
+  void* grow = (char*)a.dlogits + row * a.grow_bytes;
+  const __amdgpu_buffer_rsrc_t ws = make_rsrc(grow, (uint32_t)(a.nvec - (ragged ? 1 : 0)) * 16u);
+  const int v0 = seg * g.segvec + tid;
+  u32x4 r[K];
+  static_for<K>([&](auto I) { r[I] = bload(rs, (uint32_t)(v0 + I * BLOCK) * 16u, 0u); });
+  float coef = 0.f, b2 = INFINITY, gy = 0.f;
+  if (valid) {
+    float m = kMinRef, s = 0.f;
+    if (lane < g.nseg) {
+      const float2 p = g.part[row * g.stride + lane];
+      m = p.x;
+      s = p.y;
+    }
+    wave_lse_reduce(m, s);
+    const RowResult rr = row_epilogue<EXT, true>(a, rsc, row, m, s, g.zy[row], writer);
+    coef = rr.coef;
+    gy = coef * rr.one_m_p;
+    if (coef != 0.f) b2 = (rr.lse - logf(fabsf(coef))) * kLog2e;
+  } else if (writer) {
+    row_invalid<EXT, true>(a, rsc, row);
+  }
+  const uint32_t sgn = coef > 0.f ? E::kSignMask : 0u;
+  const int vy = valid ? (int)rsc.y / EPV : -1;
+  static_for<K>([&](auto I) {
+    const int v = v0 + I * BLOCK;
+    const u32x4 out = valid ? grad_vec<E>(r[I], b2, sgn) : u32x4{0u, 0u, 0u, 0u};
+    bstore(out, ws, (uint32_t)v * 16u, 0u);
+    if (ragged && v == a.nvec - 1)
+      for (int e = 0; e < a.V - (a.nvec - 1) * EPV; ++e)
+        E::store_elem(grow, v * EPV + e, E::elem_bits(out, e));
+    if (v == vy) E::store_elem(grow, (int)rsc.y, E::bits_of(gy));   // (after its own vector's)
+  });
+  if (seg != 0) return;
+  if (tid == 0) {
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // the row's values are visible everywhere
+    sh_last = __hip_atomic_fetch_add(g.done, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) ==
+              (uint32_t)a.T - 1;
+  }
+  __syncthreads();
+  if (!sh_last) return;
+  RowStats st{};
+  for (int64_t t = tid; t < a.T; t += BLOCK)
+    take_row(st, get_dev(fa.terms_ws + t), get_dev(fa.flags_ws + t), get_dev(fa.logk_ws + t),
+             get_dev(fa.excess_ws + t));
+  st = block_stats<BLOCK>(st);
+  if (tid == 0) write_stats(fa, st);
 }
 
 // GradParams of a row for the fused LM-head pass: the row kernel's gradient

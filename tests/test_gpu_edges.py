@@ -104,6 +104,47 @@ def test_fixed_rows_and_statistics_parts(V, T):
     test_row_queue_and_stale_workspace(V, T)
 
 
+# The row kernel's long-row variants, at and just past their capacities, with more rows than the
+# pass over segments takes (test_bf16_vocab_sizes and test_f32_vocab_sizes have fewer).
+@pytest.mark.parametrize("V,dtype", [(V, torch.bfloat16) for V in
+                                     (65536, 65537, 98304, 130001, 155648, 155649, 221185, 250001)] +
+                                    [(V, torch.float32) for V in (45001, 77824, 77825, 110593)])
+def test_row_kernel_long_rows(V, dtype):
+    epv = 8 if dtype == torch.bfloat16 else 4
+    b = make_random_batch(200, V, dtype, DEV, seed=V % 89, ld=((V + epv - 1) // epv) * epv,
+                          mask_p=0.3)
+    run_and_check(b)
+
+
+# Few long rows: the fused pass over segments (cis_seg_grad_kernel), at the first and last row
+# counts and lengths that take it and just past them (the row kernel), with ragged last vectors and
+# segments. The workspace's row counter starts as 0xFF bytes.
+@pytest.mark.parametrize("V,T,dtype", [
+    (49145, 32, torch.bfloat16), (49145, 33, torch.bfloat16), (49144, 31, torch.bfloat16),
+    (98305, 112, torch.bfloat16), (98305, 113, torch.bfloat16), (98304, 2, torch.bfloat16),
+    (155657, 192, torch.bfloat16), (155657, 193, torch.bfloat16), (262144, 5, torch.bfloat16),
+    (262145, 5, torch.bfloat16), (24577, 32, torch.float32), (131072, 40, torch.float32),
+    (131071, 7, torch.float32)])
+def test_few_long_rows(V, T, dtype):
+    epv = 8 if dtype == torch.bfloat16 else 4
+    b = make_random_batch(T, V, dtype, DEV, seed=V % 97, ld=((V + epv - 1) // epv) * epv + epv,
+                          mask_p=0.8)
+    ws = torch.full((cis.workspace_bytes(T),), 255, dtype=torch.uint8, device=DEV)
+    out, _, _ = run_and_check(b, workspace=ws)
+    # the extended kernels on the same path (CIS through the operator family: the same weights),
+    # and in place
+    prm = cis.params(cis.OP_CIS, lam=b.lam, kappa=b.kappa, scale=b.scale)
+    ext = cis.loss_bwd_ex(b.logits, b.ids, b.logp_infer, b.adv, b.mask, params=prm, V=b.V)
+    inp = cis.loss_bwd(b.logits, b.ids, b.logp_infer, b.adv, b.mask, lam=b.lam, kappa=b.kappa,
+                       scale=b.scale, V=b.V, dlogits=b.logits)
+    torch.cuda.synchronize()
+    bits = torch.int16 if dtype == torch.bfloat16 else torch.int32
+    for o in (ext, inp):
+        assert torch.equal(o["dlogits"].contiguous().view(bits),
+                           out["dlogits"].contiguous().view(bits))
+        assert torch.equal(o["terms"], out["terms"]) and torch.equal(o["loss"], out["loss"])
+
+
 # Forward pass: rows of fewer than 2048 16-byte vectors go through the row kernel (capacities
 # 128, 256, 512, 1024, 2048 vectors); rows of 2048 up to 131072 vectors through the split
 # kernels (segments of 1024, 2048 or 4096 vectors, at most 32 per row); longer rows through the
