@@ -200,7 +200,10 @@ int64_t seq_count(const LossCall& c) { return c.ext && is_seq_op(c.prm.op) ? c.n
 
 // Decoupled path: the weight depends only on (l_old, l_infer), so it is computed for all T rows
 // before any logits row is read.
-int launch_prepass(const LossCall& c, const Ws& ws, const DeviceInfo& info, hipStream_t stream) {
+// `clear_queue`: in, whether the row queue has to be cleared before the rows; out, whether it
+// still has.
+int launch_prepass(const LossCall& c, const Ws& ws, const DeviceInfo& info, bool* clear_queue,
+                   hipStream_t stream) {
   const int64_t n_seq = seq_count(c);
   cis::PrepassArgs pa{};
   if (n_seq > 0) {
@@ -224,6 +227,12 @@ int launch_prepass(const LossCall& c, const Ws& ws, const DeviceInfo& info, hipS
   pa.pflags_ws = ws.b(ws.L.pflags);
   pa.logk_ws = ws.f(ws.L.logk);
   pa.excess_ws = ws.f(ws.L.excess);
+  // it also clears the row queue, unless the pieces of log K are there
+  if (clear_queue && *clear_queue) {
+    *clear_queue = pa.pieces > 1;
+    if (!*clear_queue)
+      pa.queue = reinterpret_cast<unsigned long long*>(ws.base + cis::kQueueOff);
+  }
   return launch_grid_stride(cis::prepass_kernel(), c.T, cis::kWeightsBlock, info, &pa, stream);
 }
 
@@ -284,12 +293,12 @@ int launch_combine(const LossCall& c, cis::RowArgs& ra, cis::SegArgs& sa, int64_
              : CIS_ERR_LAUNCH;
 }
 
-// The row kernel over rows [t0, t0 + rows) of the call (see row_args).
-int launch_rows(const LossCall& c, const Ws& ws, const void* logits, void* dlogits, int64_t ld,
-                int64_t ld_g, int64_t t0, int64_t rows, int dev, const DeviceInfo& info,
-                hipStream_t stream) {
-  if (rows <= 0) return CIS_OK;
-  cis::RowArgs ra = row_args(c, ws, logits, dlogits, ld, ld_g, t0, rows);
+// The row kernel (or the split forward pass) over the call's rows. `clear_queue`: the row queue's
+// counters have not been cleared yet.
+int launch_rows(const LossCall& c, const Ws& ws, bool clear_queue, int dev,
+                const DeviceInfo& info, hipStream_t stream) {
+  const int64_t rows = c.T;
+  cis::RowArgs ra = row_args(c, ws, c.logits, c.dlogits, c.ld, c.ld_g, 0, rows);
   const int32_t nvec = ra.nvec;
   const cis::RowVariant& var = c.ext ? cis::select_row_variant_ext(c.dtype, c.bwd, nvec)
                                      : cis::select_row_variant(c.dtype, c.bwd, nvec);
@@ -300,8 +309,8 @@ int launch_rows(const LossCall& c, const Ws& ws, const void* logits, void* dlogi
     cis::SegArgs sa{};
     sa.segvec = sv->block * sv->k;
     sa.nseg = (int32_t)((nvec + sa.segvec - 1) / sa.segvec);
-    sa.part = reinterpret_cast<float2*>(ws.base + ws.L.part) + t0 * cis::kSegMax;
-    sa.zy = ws.f(ws.L.zy) + t0;
+    sa.part = reinterpret_cast<float2*>(ws.base + ws.L.part);
+    sa.zy = ws.f(ws.L.zy);
     sa.stride = cis::kSegMax;
     void* args[] = {&ra, &sa};
     // one short-lived workgroup per (row, segment); the kernel loops only past 2^30 of them
@@ -318,7 +327,7 @@ int launch_rows(const LossCall& c, const Ws& ws, const void* logits, void* dlogi
   // the fused pass takes its rows from a queue, except one-wave rows and a workgroup's first
   // three (see cis_row_kernel)
   if (!c.bwd || var.block <= 64 || rows <= 3 * (int64_t)grid) ra.queue = nullptr;
-  if (ra.queue) {
+  if (ra.queue && clear_queue) {
     void* qargs[] = {&ra.queue};
     if (hipLaunchKernel(cis::queue_reset_kernel(), dim3(1), dim3(64), qargs, 0, stream) !=
         hipSuccess)
@@ -361,7 +370,7 @@ int launch_seg_grad(const LossCall& c, const Ws& ws, const cis::SegGradVariant& 
   sa.part = reinterpret_cast<float2*>(ws.base + ws.L.part);
   sa.zy = ws.f(ws.L.zy);
   sa.stride = cis::kSegMax;
-  sa.done = reinterpret_cast<uint32_t*>(ws.base + cis::kQueueOff);
+  sa.done = reinterpret_cast<uint32_t*>(ws.base + cis::kDoneOff);
   cis::FinalizeArgs fa = finalize_args(ws, c.T, c.loss_out, c.stats_out);
   const unsigned grid = (unsigned)(c.T * sa.nseg);
   void* sargs[] = {&ra, &sa};
@@ -416,12 +425,12 @@ int run_loss(const LossCall& c, hipStream_t stream) {
 
   const Ws ws{static_cast<char*>(c.workspace), L};
   if (T > 0) {
+    bool clear_queue = bwd;
     if (c.logp_old) {
-      if (int rc = launch_prepass(c, ws, info, stream)) return rc;
+      if (int rc = launch_prepass(c, ws, info, &clear_queue, stream)) return rc;
     }
     if (few) return launch_seg_grad(c, ws, sg, stream);
-    if (int rc = launch_rows(c, ws, c.logits, c.dlogits, c.ld, c.ld_g, 0, T, dev, info, stream))
-      return rc;
+    if (int rc = launch_rows(c, ws, clear_queue, dev, info, stream)) return rc;
   }
   return launch_finalize(ws, T, c.loss_out, stream, c.stats_out);
 }
@@ -531,7 +540,7 @@ int run_lmhead(const LmHeadCall& m, hipStream_t stream) {
       return rc;
   }
   if (T > 0 && c.logp_old) {
-    if (int rc = launch_prepass(c, ws, info, stream)) return rc;
+    if (int rc = launch_prepass(c, ws, info, nullptr, stream)) return rc;
   }
   const int64_t group = cis::lm_dw_rows(m.chunk);  // rows per dL/dW product
   for (int64_t t0 = 0; t0 < T; t0 += m.chunk) {

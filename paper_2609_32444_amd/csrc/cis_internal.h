@@ -10,7 +10,8 @@
 namespace cis {
 
 // Workspace layout (bytes), every array 256-byte aligned:
-//   [0, 256)     cis_stats_t
+//   [0, 256)     cis_stats_t, and from 128 the counter by which a kernel's last workgroup knows
+//                itself (cleared by the kernel before it)
 //   [256, 1280)  the fused pass's row-queue counters, one per 128-byte line; before the rows,
 //                the pieces of the responses' log K, where there are several (kSeqPieceSums)
 //   terms  float[T]   per-row loss term
@@ -33,6 +34,8 @@ static_assert(sizeof(cis_stats_t) <= kStatsBytes, "the statistics fit their bloc
 // which short rows approach (one draw per row); counters on separate lines are served in
 // parallel. Short rows use all of them, long rows one (with eight, the long-row workloads ran
 // 2-3% slower).
+constexpr size_t kDoneOff = 128;   // counter of finished rows, in the same block
+static_assert(sizeof(cis_stats_t) <= kDoneOff, "the counter follows the statistics");
 constexpr int kRowQueues = 8;
 constexpr size_t kQueueOff = kStatsBytes;
 constexpr size_t kQueueStride = 128;
@@ -310,6 +313,7 @@ struct PrepassArgs {
   float* logk_ws;           // nullable (loss path), as excess_ws
   float* excess_ws;
   RowStats* parts;          // nullable: weights path: each workgroup's statistics
+  unsigned long long* queue;  // nullable: row-queue counters to clear (loss path)
 };
 
 // A compiled row-kernel variant: BLOCK threads per workgroup, NV register-resident 16-byte

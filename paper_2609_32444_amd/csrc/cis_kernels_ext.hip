@@ -126,6 +126,8 @@ __device__ __forceinline__ float seq_weight(const PrepassArgs& a, int64_t s, boo
 __global__ __launch_bounds__(kWeightsBlock) void cis_prepass_kernel(const PrepassArgs a) {
   __shared__ float sh_w[kWeightsBlock];
   __shared__ bool sh_acted[kWeightsBlock];
+  if (a.queue && blockIdx.x == 0 && threadIdx.x < kRowQueues)
+    a.queue[threadIdx.x * (kQueueStride / sizeof(*a.queue))] = 0ull;
   const bool seq = a.ops.op == CIS_OP_SEQ_TIS || a.ops.op == CIS_OP_SEQ_MIS;
   RowStats st{};
   for (int64_t t0 = (int64_t)blockIdx.x * kWeightsBlock; t0 < a.T;

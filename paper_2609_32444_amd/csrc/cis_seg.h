@@ -162,11 +162,7 @@ __global__ __launch_bounds__(BLOCK) void cis_seg_grad_kernel(const RowArgs a, co
     if (v == vy) E::store_elem(grow, (int)rsc.y, E::bits_of(gy));   // (after its own vector's)
   });
   if (seg != 0) return;
-  if (tid == 0) {
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // the row's values are visible everywhere
-    sh_last = __hip_atomic_fetch_add(g.done, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) ==
-              (uint32_t)a.T - 1;
-  }
+  if (tid == 0) sh_last = last_done(g.done, (uint32_t)a.T);
   __syncthreads();
   if (!sh_last) return;
   RowStats st{};
