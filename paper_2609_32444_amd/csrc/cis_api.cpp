@@ -523,22 +523,13 @@ int run_lmhead(const LmHeadCall& m, hipStream_t stream) {
   char* base = static_cast<char*>(c.workspace);
   const Ws ws{base, LM.loss};
   float* Z = reinterpret_cast<float*>(base + LM.z);
-  __bf16* Wt = reinterpret_cast<__bf16*>(base + LM.wt);
-  __bf16* Gt = reinterpret_cast<__bf16*>(base + LM.gt);
-  __bf16* Ht = reinterpret_cast<__bf16*>(base + LM.ht);
-  __bf16* Gb = reinterpret_cast<__bf16*>(base + LM.gb);
+  __bf16* G = reinterpret_cast<__bf16*>(base + LM.g);
   float* part = reinterpret_cast<float*>(base + LM.part);
   cis::GemmQueuePool queues{reinterpret_cast<int*>(base + LM.queue)};
   auto ok = [](hipError_t e) { return e == hipSuccess ? CIS_OK : CIS_ERR_LAUNCH; };
   const __bf16* hid = static_cast<const __bf16*>(m.hidden);
   const int ncu = info.num_cu;
 
-  if (bwd && T > 0) {  // W^T once: the operand of dL/dh = G W with V as the contracted axis
-    if (int rc = ok(cis::launch_transpose(
-            cis::TransposeArgs{m.weight, Wt, nullptr, V, H, m.ld_w, LM.ldv, 0, nullptr}, false,
-            stream)))
-      return rc;
-  }
   if (T > 0 && c.logp_old) {
     if (int rc = launch_prepass(c, ws, info, nullptr, stream)) return rc;
   }
@@ -550,9 +541,9 @@ int run_lmhead(const LmHeadCall& m, hipStream_t stream) {
     // The logits product's epilogue leaves per row and 64-column block a (max, exp-sum) pair
     // (and the sampled logit); the combine folds a row's pairs in column order, runs the loss
     // epilogue and, for the backward, writes the row's gradient parameters. The default
-    // backward also stores the chunk's logits in float32 and forms G and G^T from them in one
-    // tiled pass; the forward, and the backward with `recompute`, never store them (the
-    // backward forms the product a second time, with an epilogue that writes G).
+    // backward also stores the chunk's logits in float32 and forms G from them; the forward, and
+    // the backward with `recompute`, never store them (the backward forms the product a second
+    // time, with an epilogue that writes G).
     cis::GemmArgs ga = cis::gemm_args(hc, m.weight, LM.fused ? nullptr : Z, tc, V, H, m.ld_h,
                                       m.ld_w, LM.fused ? 0 : LM.ldz);
     ga.epi = LM.fused ? cis::kEpiLse : cis::kEpiLseStore;
@@ -570,47 +561,36 @@ int run_lmhead(const LmHeadCall& m, hipStream_t stream) {
     sa.gp = bwd ? reinterpret_cast<cis::GradParams*>(base + LM.tgp) : nullptr;
     if (int rc = launch_combine(c, ra, sa, tc, stream)) return rc;
     if (!bwd) continue;
+    __bf16* Gc = G + (t0 - g0) * LM.ldv;   // the chunk's rows of the group's G
     if (LM.fused) {
       ga.epi = cis::kEpiGrad;
       ga.e.gp = sa.gp;
-      ga.e.G = Gb;
+      ga.e.G = Gc;
       ga.e.ldg = LM.ldv;
       if (int rc = ok(cis::launch_gemm_epi(ga, queues, ncu, stream))) return rc;
-      // G^T (operand of dL/dW) into the group's columns t0 - g0 ..
-      if (int rc = ok(cis::launch_transpose(
-              cis::TransposeArgs{Gb, Gt + (t0 - g0), nullptr, tc, V, LM.ldv, LM.ldc, 0, nullptr},
-              false, stream)))
-        return rc;
     } else {
-      // G = dL/dz in bf16 (operand of dL/dh) and G^T (operand of dL/dW, the group's columns
-      // t0 - g0 ..) from the stored logits
-      if (int rc = ok(cis::launch_transpose(
-              cis::TransposeArgs{Z, Gt + (t0 - g0), Gb, tc, V, LM.ldz, LM.ldc, LM.ldv, sa.gp},
-              true, stream)))
+      if (int rc = ok(cis::launch_grad(cis::GradArgs{Z, Gc, sa.gp, tc, V, LM.ldz, LM.ldv}, stream)))
         return rc;
     }
-    // h_c^T (operand of dL/dW)
-    if (int rc = ok(cis::launch_transpose(
-            cis::TransposeArgs{hc, Ht + (t0 - g0), nullptr, tc, H, m.ld_h, LM.ldc, 0, nullptr},
-            false, stream)))
-      return rc;
-    // dL/dh_c = G W = G (W^T)^T
-    if (int rc = ok(cis::launch_gemm_nt(
-            cis::gemm_args(Gb, Wt, m.dhidden + t0 * m.ld_dh, tc, H, V, LM.ldv, LM.ldv, m.ld_dh),
-            false, part, LM.splits, queues, ncu, stream)))
+    // dL/dh_c = G W
+    if (int rc = ok(cis::launch_gemm(
+            cis::gemm_args(Gc, m.weight, m.dhidden + t0 * m.ld_dh, tc, H, V, LM.ldv, m.ld_w,
+                           m.ld_dh),
+            false, false, part, LM.splits, queues, ncu, stream)))
       return rc;
     // dL/dW (+)= G^T h over the group's rows, once its last chunk is in
     const int64_t gend = g0 + group < T ? g0 + group : T;
     if (t0 + tc < gend) continue;
-    if (int rc = ok(cis::launch_gemm_nt(
-            cis::gemm_args(Gt, Ht, m.dweight, V, H, gend - g0, LM.ldc, LM.ldc, m.ld_dw),
-            m.accumulate || g0 > 0, nullptr, 1, queues, ncu, stream)))
+    if (int rc = ok(cis::launch_gemm(
+            cis::gemm_args(G, hid + g0 * m.ld_h, m.dweight, V, H, gend - g0, LM.ldv, m.ld_h,
+                           m.ld_dw),
+            true, m.accumulate || g0 > 0, nullptr, 1, queues, ncu, stream)))
       return rc;
   }
   if (bwd && T == 0 && !m.accumulate) {  // no rows: dL/dW = 0 (an empty contraction)
-    if (int rc = ok(cis::launch_gemm_nt(
-            cis::gemm_args(Wt, Wt, m.dweight, V, H, 0, 8, 8, m.ld_dw), false, nullptr, 1, queues,
-            ncu, stream)))
+    if (int rc = ok(cis::launch_gemm(
+            cis::gemm_args(m.weight, m.weight, m.dweight, V, H, 0, 8, 8, m.ld_dw), true, false,
+            nullptr, 1, queues, ncu, stream)))
       return rc;
   }
   return launch_finalize(ws, T, c.loss_out, stream);

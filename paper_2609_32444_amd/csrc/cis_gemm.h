@@ -27,10 +27,12 @@ struct GemmEpi {
   int64_t ldg;
 };
 
-// C[M, N] (float32, row stride ldc) = alpha * A[M, K] * B[N, K]^T (+ C when accumulating), or
-// one of the row-loss epilogues above instead of C. A and B are bf16, row-major with K
-// contiguous (row strides lda, ldb: multiples of 8 elements, bases 16-byte aligned). Any M, N,
-// K >= 0. The fields after alpha are set by launch_gemm_nt.
+// C[M, N] (float32, row stride ldc) = alpha * A * B (+ C when accumulating), or one of the row-loss
+// epilogues above instead of C. A and B are bf16. For the epilogues A is [M, K] and B is [N, K],
+// both row-major; for launch_gemm B is [K, N] and A is [M, K], or [K, M] with a_kmajor. Row strides
+// lda, ldb are multiples of 8 elements, at most 2^22, and bases 16-byte aligned; a matrix's rows
+// are mapped up to a multiple of 8 elements. Any M, N, K >= 0. The fields after alpha are set by
+// the launches.
 struct GemmArgs {
   const void* A;
   const void* B;
@@ -63,24 +65,19 @@ inline GemmArgs gemm_args(const void* A, const void* B, float* C, int64_t M, int
   return g;
 }
 
-// out[c][r] = bf16(f(in[r][c])), in R x C (float32 or bf16, row stride ldi), out C x R (ldo);
-// out_n (nullable) receives bf16(f(in)) in the input's layout (row stride ldn). f is the
-// identity, or with gp (float32 input only) the loss gradient of logit in[r][c] from row r's
-// GradParams (the kEpiGrad formula). Row strides are multiples of 4 elements and bases
-// 16-byte aligned.
-struct TransposeArgs {
-  const void* in;
-  void* out;
-  void* out_n;
-  int64_t R, C, ldi, ldo, ldn;
+// G (bf16, row stride ldg) = the loss gradient of the logits Z (float32, row stride ldz), from
+// each row's GradParams. Row strides are multiples of 8 elements and bases 16-byte aligned.
+struct GradArgs {
+  const float* Z;
+  __bf16* G;
   const GradParams* gp;
+  int64_t rows, V, ldz, ldg;
 };
 
 constexpr int kGemmTile = 256;      // C tile per workgroup (rows and columns)
 constexpr int kGemmBK = 64;         // contraction slab
 constexpr int kGemmWaveM = 128;     // C tile per wave: 128 rows x 64 columns (8 waves)
 constexpr int kGemmWaveN = 64;
-constexpr int kTransposeTile = 64;
 constexpr int kGemmQueues = 8;      // one work queue per XCD
 
 // Device scratch for the products' work queues, one set of kGemmQueues counters per product. A
@@ -93,7 +90,7 @@ struct GemmQueuePool {
   hipError_t take(int** queue, hipStream_t stream);
 };
 
-// Number of K splits, up to max_splits, that launch_gemm_nt uses for an M x N x K product.
+// Number of K splits, up to max_splits, that launch_gemm uses for an M x N x K product.
 int64_t gemm_splitk_count(int64_t M, int64_t N, int64_t K, int64_t max_splits, int num_cu);
 
 // Launch on `stream`; `beta` adds the product to C instead of overwriting it. With `partial`
@@ -101,11 +98,11 @@ int64_t gemm_splitk_count(int64_t M, int64_t N, int64_t K, int64_t max_splits, i
 // the partials summed in a fixed order. With more tiles than CUs, one workgroup per CU takes tiles from per-XCD queues until all are taken, so XCDs that run faster
 // take over tiles of slower ones. Results do not depend on it: a tile is computed the same way
 // by whichever workgroup takes it.
-hipError_t launch_gemm_nt(GemmArgs g, bool beta, float* partial, int64_t max_splits,
-                          GemmQueuePool& queues, int num_cu, hipStream_t stream);
+hipError_t launch_gemm(GemmArgs g, bool a_kmajor, bool beta, float* partial, int64_t max_splits,
+                       GemmQueuePool& queues, int num_cu, hipStream_t stream);
 // The logits product of a row chunk with a row-loss epilogue (kEpiLse, kEpiGrad or
 // kEpiLseStore; no split-K; C only with kEpiLseStore): M rows of h, N = V columns of W.
 hipError_t launch_gemm_epi(GemmArgs g, GemmQueuePool& queues, int num_cu, hipStream_t stream);
-hipError_t launch_transpose(TransposeArgs t, bool in_f32, hipStream_t stream);
+hipError_t launch_grad(const GradArgs& t, hipStream_t stream);
 
 }  // namespace cis

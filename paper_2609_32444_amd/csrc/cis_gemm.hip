@@ -1,7 +1,7 @@
-// Dense products of the LM-head form (gfx950 MFMA): C = alpha * A * B^T (+ C), both operands
-// bf16 and K-contiguous, float32 accumulation; and a tiled transpose that converts to bf16. Used
-// for the logits of a row chunk (hidden * W^T), the gradient with respect to the hidden states
-// (G * W) and the gradient of the head weight (G^T * hidden).
+// Dense products of the LM-head form (gfx950 MFMA): bf16 operands, row-major (K contiguous) or
+// k-major in memory, float32 accumulation. Used for the logits of a row chunk (hidden * W^T, both
+// row-major), the gradient with respect to the hidden states (G * W, W k-major) and the gradient
+// of the head weight (G^T * hidden, both k-major); and G from stored logits.
 //
 // Tiling: a workgroup of 8 waves owns a 256 x 256 tile of C; each wave owns 128 x 64 as 8 x 4
 // blocks of v_mfma_f32_16x16x32_bf16 (which sustains about 98% of the matrix cores' peak on this
@@ -32,6 +32,7 @@ namespace {
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
+typedef __attribute__((address_space(3))) bf16x4* lds_bf16x4;
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
@@ -288,12 +289,15 @@ struct EpiRows<kEpiGrad> {
 template <>
 struct EpiRows<kEpiStore> {};
 
-// The operands of one unit: resources at its tile's first rows, and its contraction range.
+// The operands of one unit, and its contraction range: of a row-major operand a resource at its
+// tile's first row, of a k-major one the address of its tile's first column.
 struct UnitSrc {
   __amdgpu_buffer_rsrc_t a, b;
+  const __bf16 *pa, *pb;
   uint32_t m0, n0, split;
   int kbeg, kend;
 };
+template <bool KMA, bool KMB>
 __device__ __forceinline__ UnitSrc unit_src(const GemmArgs& g, int u) {
   UnitSrc s;
   uint32_t tm = 0, tn = 0;
@@ -302,13 +306,29 @@ __device__ __forceinline__ UnitSrc unit_src(const GemmArgs& g, int u) {
   s.m0 = tm * kGemmTile;
   s.n0 = tn * kGemmTile;
   s.kbeg = (int)(s.split * g.k_split);
+  // (u < 0: nothing to contract and empty resources, so that the loads ahead of the last tile
+  // read nothing)
   s.kend = u < 0 ? s.kbeg : (int)(s.kbeg + g.k_split < g.K ? s.kbeg + g.k_split : g.K);
-  // (u < 0: empty resources, so that the loads ahead of the last tile read nothing)
-  s.a = make_rsrc(static_cast<const __bf16*>(g.A) + (int64_t)s.m0 * g.lda,
-                  u < 0 ? 0 : span_bytes(g.M, s.m0, g.K, g.lda));
-  s.b = make_rsrc(static_cast<const __bf16*>(g.B) + (int64_t)s.n0 * g.ldb,
-                  u < 0 ? 0 : span_bytes(g.N, s.n0, g.K, g.ldb));
+  const __bf16 *A = static_cast<const __bf16*>(g.A), *B = static_cast<const __bf16*>(g.B);
+  s.pa = A + s.m0;
+  s.pb = B + s.n0;
+  if (!KMA)
+    s.a = make_rsrc(A + (int64_t)s.m0 * g.lda, u < 0 ? 0 : span_bytes(g.M, s.m0, g.K, g.lda));
+  if (!KMB)
+    s.b = make_rsrc(B + (int64_t)s.n0 * g.ldb, u < 0 ? 0 : span_bytes(g.N, s.n0, g.K, g.ldb));
   return s;
+}
+
+// The unit's operands at row k of the contraction. A k-major operand's resource starts at that row
+// and ends with the contraction's last one, so rows at or past kend read as zero; columns past the
+// matrix are read where they lie within it (they reach only results that are not stored).
+// (Formed right before an operand's loads, with 32-bit arithmetic where it can be: scalar
+// instructions ahead of the first phase held both waves of a SIMD up, 8% of the product.)
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t slab_rsrc(const __bf16* p, uint32_t cols,
+                                                            uint32_t ld, uint32_t k, int left) {
+  const uint32_t last = ((uint32_t)(left - 1) * ld + ((cols + 7) & ~7u)) * 2;   // left <= 64
+  const uint32_t n = left > kGemmBK ? kOobBase : last;
+  return make_rsrc((const char*)p + (uint64_t)k * (uint64_t)(ld * 2), left <= 0 ? 0 : n);
 }
 
 // The products. A workgroup works through units (tiles, or a tile's share of a split
@@ -338,9 +358,17 @@ __device__ __forceinline__ UnitSrc unit_src(const GemmArgs& g, int u) {
 // clock falls to 1.67-1.71 GHz (1423-1535 TFLOP/s without an epilogue). Products of the rollout
 // batch, before (one slab ahead, every fragment read behind the slab's barrier) and now:
 // logits with pairs, 4096 x 151936 x 2048, 2.07 and 1.84 ms; with the stored chunk 2.65 and
-// 2.42 ms; dL/dh, 4096 x 2048 x 151936, 1.97 and 1.72 ms; dL/dW, 151936 x 2048 x 16384, 8.62
-// and 7.49 ms.
-template <bool BETA, int EPI>
+// 2.38 ms; dL/dh, 4096 x 2048 x 151936, 1.97 and 1.79 ms (1.68 with a transposed copy of W, which
+// takes 0.22 ms per call); dL/dW, 151936 x 2048 x 16384, 8.62 and 7.39 ms (7.30 with transposed
+// copies of G and h, for which a chunk's G and G^T took 1.03 ms instead of 0.65 ms for G).
+//
+// KMA, KMB: the operand is k-major in memory, [K, M] or [K, N], so a product needs no transposed
+// copy. Its piece of a slab is 64 rows of 128 columns (256 bytes) in LDS, and a fragment is read
+// by two transposing reads (ds_read_b64_tr_b16: within 16 lanes, lane 4a + b receives element b
+// of the 8 bytes of lanes a, 4 + a, 8 + a and 12 + a). The 32-byte block c of row k is stored at
+// block c ^ (k & 3 | (k >> 3 & 1) << 2): the eight rows that half a wave reads at once lie in
+// different banks.
+template <bool BETA, int EPI, bool KMA, bool KMB>
 __global__ __launch_bounds__(kThreads) void gemm_bf16_kernel(const GemmArgs g) {
   // A's pieces (slab 0: A0, A1, slab 1: A0, A1), then B's: every fragment of an operand lies
   // within the 16-bit offset of one address
@@ -363,36 +391,82 @@ __global__ __launch_bounds__(kThreads) void gemm_bf16_kernel(const GemmArgs g) {
   // (row & 7). Slab rows to tile rows: a piece holds, per wave row (column) of the tile, 64 (32)
   // of its rows (columns), so that a wave's tile stays contiguous: piece h's row 64 j + x of A is
   // tile row 128 j + 64 h + x, row 32 c + x of B tile row 64 c + 32 h + x.
+  // k-major: load j fills rows 32 j + 4 wave + lane / 16, stored chunk lane % 16 (half of a
+  // 32-byte block) holding the logical block (lane % 16 / 2) ^ the row's swizzle.
   const int lchunk8 = ((lane & 7) ^ ((lane >> 3) & 7)) * 8;
-  const uint32_t va = (uint32_t)(((wave * 8 + (lane >> 3)) * g.lda + lchunk8) * 2);
+  const int kcol = (((lane & 15) >> 1) ^ ((lane >> 4) | (((wave >> 1) & 1) << 2))) * 16 +
+                   (lane & 1) * 8;   // column within a k-major piece
+  const uint32_t va =
+      KMA ? (uint32_t)(((wave * 4 + (lane >> 4)) * g.lda + kcol / 64 * 128 + kcol % 64) * 2)
+          : (uint32_t)(((wave * 8 + (lane >> 3)) * g.lda + lchunk8) * 2);
   const uint32_t vb =
-      (uint32_t)(((wave / 4 * 64 + wave % 4 * 8 + (lane >> 3)) * g.ldb + lchunk8) * 2);
-  const uint32_t sa = (uint32_t)(64 * g.lda * 2), sb = (uint32_t)(32 * g.ldb * 2);
-  // operand op (0: A, 1: B), piece h, of the slab at k into buffer b. Chunks at or past kend read
-  // as zero; one that straddles kend is cleared by fix().
-  auto load = [&](int op, int h, int b, const UnitSrc& s, int k) {
-    const uint32_t step = op ? sb : sa;
-    const uint32_t v = (lchunk8 < s.kend - k ? (op ? vb : va) : kOobBase) + h * step;
-    load_lds16x2(op ? s.b : s.a, lds0 + op * kOpBytes + (2 * b + h) * kPieceBytes, v,
-                 v + (op ? 4 : 2) * step, (uint32_t)(k * 2));
+      KMB ? (uint32_t)(((wave * 4 + (lane >> 4)) * g.ldb + kcol / 32 * 64 + kcol % 32) * 2)
+          : (uint32_t)(((wave / 4 * 64 + wave % 4 * 8 + (lane >> 3)) * g.ldb + lchunk8) * 2);
+  // the resource of operand op (0: A, 1: B) for unit s's slab at k
+  auto rsrc = [&](int op, const UnitSrc& s, int k) {
+    if (op ? KMB : KMA)
+      return op ? slab_rsrc(s.pb, (uint32_t)(g.N - s.n0), (uint32_t)g.ldb, k, s.kend - k)
+                : slab_rsrc(s.pa, (uint32_t)(g.M - s.m0), (uint32_t)g.lda, k, s.kend - k);
+    return op ? s.b : s.a;
   };
-  // Fragment addresses: lane holds row 16 i + lane % 16 of its piece, logical chunk
+  // operand op, piece h, of the slab at k of a contraction up to kend, into buffer b, through
+  // resource r. Chunks at or past kend read as zero; one of a row-major operand that straddles it
+  // is cleared by fix().
+  auto load = [&](int op, int h, int b, __amdgpu_buffer_rsrc_t r, int k, int kend) {
+    const bool km = op ? KMB : KMA;
+    const uint32_t ld2 = (uint32_t)((op ? g.ldb : g.lda) * 2);
+    const uint32_t lds = lds0 + op * kOpBytes + (2 * b + h) * kPieceBytes;
+    if (km) {
+      const uint32_t v = (op ? vb : va) + h * (op ? 64 : 128);
+      load_lds16x2(r, lds, v, v + 32 * ld2, 0);
+    } else {
+      const uint32_t step = (op ? 32 : 64) * ld2;
+      const uint32_t v = (lchunk8 < kend - k ? (op ? vb : va) : kOobBase) + h * step;
+      load_lds16x2(r, lds, v, v + (op ? 4 : 2) * step, (uint32_t)(k * 2));
+    }
+  };
+  // Fragment addresses. Row-major: lane holds row 16 i + lane % 16 of its piece, logical chunk
   // 4 s + lane / 16; a block's first row is a multiple of 16, so the swizzle is lane & 7.
+  // k-major: lane 4 r + a of a group g of 16 reads row 8 g + r (then 8 g + 4 + r) of step s,
+  // columns 4 a .. 4 a + 3 of block i, and holds column lane % 16 with k = 8 g ... 8 g + 7.
   const int fr = lane & 15, fq = lane >> 4, sw = lane & 7;
-  const char* fa[2];
+  const int kr = fr >> 2, ksw = kr | ((fq & 1) << 2);
+  const char* fa[KMA ? kTm / 2 : 2];
   const char* fb[2];
 #pragma unroll
   for (int s = 0; s < 2; ++s) {
     const int c = ((4 * s + fq) ^ sw) * 16;
-    fa[s] = lds + (wm * 64 + fr) * 128 + c;
-    fb[s] = lds + kOpBytes + (wn * 32 + fr) * 128 + c;
+    if (!KMA) fa[s] = lds + (wm * 64 + fr) * 128 + c;
+    if (!KMB) fb[s] = lds + kOpBytes + (wn * 32 + fr) * 128 + c;
   }
+  const char* krow = lds + (8 * fq + kr) * 256 + (lane & 3) * 8;
+  if constexpr (KMA) {
+#pragma unroll
+    for (int i = 0; i < kTm / 2; ++i) fa[i] = krow + ((wm * 4 + i) ^ ksw) * 32;
+  }
+  if constexpr (KMB) {
+#pragma unroll
+    for (int i = 0; i < kTn / 2; ++i) fb[i] = krow + kOpBytes + ((wn * 2 + i) ^ ksw) * 32;
+  }
+  auto read_tr = [&](const char* p) {
+    const bf16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lds_bf16x4)p);
+    const bf16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lds_bf16x4)(p + 4 * 256));
+    return __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
+  };
   bf16x8 a0[kTm / 2][2], a1[kTm / 2][2], b0[kTn / 2][2], b1[kTn / 2][2];
   auto read_a = [&](bf16x8(&f)[kTm / 2][2], int h, int b, int q) {
-    f[q % 4][q / 4] = *(const bf16x8*)(fa[q / 4] + (2 * b + h) * kPieceBytes + (q % 4) * 2048);
+    const int i = q % 4, s = q / 4, o = (2 * b + h) * kPieceBytes;
+    if constexpr (KMA)
+      f[i][s] = read_tr(fa[i] + o + s * 32 * 256);
+    else
+      f[i][s] = *(const bf16x8*)(fa[s] + o + i * 2048);
   };
   auto read_b = [&](bf16x8(&f)[kTn / 2][2], int h, int b, int q) {
-    f[q % 2][q / 2] = *(const bf16x8*)(fb[q / 2] + (2 * b + h) * kPieceBytes + (q % 2) * 2048);
+    const int i = q % 2, s = q / 2, o = (2 * b + h) * kPieceBytes;
+    if constexpr (KMB)
+      f[i][s] = read_tr(fb[i] + o + s * 32 * 256);
+    else
+      f[i][s] = *(const bf16x8*)(fb[s] + o + i * 2048);
   };
   f32x4 acc[kTm][kTn];
   // One phase: the MFMAs of an A piece with a B piece, a fragment read (q = 0..7, if any) ahead of
@@ -423,11 +497,11 @@ __global__ __launch_bounds__(kThreads) void gemm_bf16_kernel(const GemmArgs g) {
 #pragma unroll
     for (int x = 0; x < 8; ++x)
       if (x >= kend % 8) e[x] = (__bf16)0.f;
-    *(bf16x8*)p = e;
+    if (tid < 256 || !KMB) *(bf16x8*)p = e;   // (A's 256 rows, then B's)
     lds_barrier();
   };
   auto tail_slab = [](const UnitSrc& s) {   // the slab that fix() is for, or -1
-    return s.kend % 8 ? (s.kend - s.kbeg) / kGemmBK : -1;
+    return !KMA && s.kend % 8 ? (s.kend - s.kbeg) / kGemmBK : -1;
   };
   // requests for the epilogue's inputs of unit s's rows, and their store to LDS
   auto epi_id = [&](const UnitSrc& s) -> int64_t {
@@ -446,15 +520,16 @@ __global__ __launch_bounds__(kThreads) void gemm_bf16_kernel(const GemmArgs g) {
     }
   };
 
-  UnitSrc cur = unit_src(g, u);
+  UnitSrc cur = unit_src<KMA, KMB>(g, u);
   // the first two slabs, in the order in which the stream requests pieces
 #pragma unroll
   for (int b = 0; b < 2; ++b) {
     const int k = cur.kbeg + b * kGemmBK;
-    load(0, 0, b, cur, k);
-    load(1, b, b, cur, k);
-    load(1, 1 - b, b, cur, k);
-    load(0, 1, b, cur, k);
+    const __amdgpu_buffer_rsrc_t ra = rsrc(0, cur, k), rb = rsrc(1, cur, k);
+    load(0, 0, b, ra, k, cur.kend);
+    load(1, b, b, rb, k, cur.kend);
+    load(1, 1 - b, b, rb, k, cur.kend);
+    load(0, 1, b, ra, k, cur.kend);
   }
   epi_put(er[0], epi_id(cur), epi_gp(cur));
   if (tid == 0) sh_unit[0] = next_unit(g, home, tried);
@@ -467,7 +542,7 @@ __global__ __launch_bounds__(kThreads) void gemm_bf16_kernel(const GemmArgs g) {
 #pragma unroll
     for (int q = 0; q < 4; ++q) read_b(b0, 0, 0, q);
     const int un = __builtin_amdgcn_readfirstlane(sh_unit[p]);
-    const UnitSrc nxt = unit_src(g, un);
+    const UnitSrc nxt = unit_src<KMA, KMB>(g, un);
     lds_barrier();   // every wave has read A0 and B0
 #pragma unroll
     for (int i = 0; i < kTm; ++i)
@@ -478,34 +553,34 @@ __global__ __launch_bounds__(kThreads) void gemm_bf16_kernel(const GemmArgs g) {
                                        : 2;
     for (int kt = 0; kt < nk; kt += 2) {
       const bool last = kt + 2 >= nk;
-      UnitSrc s;     // of the slabs two ahead
-      s.a = last ? nxt.a : cur.a;
-      s.b = last ? nxt.b : cur.b;
-      s.kend = last ? nxt.kend : cur.kend;
+      // the slabs two ahead: this unit's, or the next one's first two
+      UnitSrc su = cur;
+      if (last) su = nxt;
       const int k2 = last ? nxt.kbeg : cur.kbeg + (kt + 2) * kGemmBK, k3 = k2 + kGemmBK;
+      __amdgpu_buffer_rsrc_t ra, rb;
       // even slab
       phase(0, 0, a0, b0, [&](int q) { if (q < 4) read_b(b1, 1, 0, q); },
-            [&] { load(0, 0, 0, s, k2); });
+            [&] { ra = rsrc(0, su, k2); load(0, 0, 0, ra, k2, su.kend); });
       phase(0, 1, a0, b1, [&](int q) { read_a(a1, 1, 0, q); },
-            [&] { load(1, 0, 0, s, k2); });
+            [&] { rb = rsrc(1, su, k2); load(1, 0, 0, rb, k2, su.kend); });
       if (kt + 1 == tail) fix(1, cur.kend);
       wait_barrier<2 * kGroupLoads>();
       phase(1, 1, a1, b1, [&](int q) { read_a(a0, 0, 1, q); },
-            [&] { load(1, 1, 0, s, k2); });
+            [&] { load(1, 1, 0, rb, k2, su.kend); });
       phase(1, 0, a1, b0, [&](int q) { if (q < 4) read_b(b1, 1, 1, q); },
-            [&] { load(0, 1, 0, s, k2); });
+            [&] { load(0, 1, 0, ra, k2, su.kend); });
       wait_barrier<2 * kGroupLoads>();
       // odd slab
       phase(0, 1, a0, b1, [&](int q) { if (q < 4) read_b(b0, 0, 1, q); },
-            [&] { load(0, 0, 1, s, k3); });
+            [&] { ra = rsrc(0, su, k3); load(0, 0, 1, ra, k3, su.kend); });
       phase(0, 0, a0, b0, [&](int q) { read_a(a1, 1, 1, q); },
-            [&] { load(1, 1, 1, s, k3); });
-      if (last ? tail_nxt == 0 : kt + 2 == tail) fix(0, s.kend);
+            [&] { rb = rsrc(1, su, k3); load(1, 1, 1, rb, k3, su.kend); });
+      if (last ? tail_nxt == 0 : kt + 2 == tail) fix(0, su.kend);
       wait_barrier<2 * kGroupLoads>();
       phase(1, 0, a1, b0, [&](int q) { read_a(a0, 0, 0, q); },
-            [&] { load(1, 0, 1, s, k3); });
+            [&] { load(1, 0, 1, rb, k3, su.kend); });
       phase(1, 1, a1, b1, [&](int q) { if (q < 4) read_b(b0, 0, 0, q); },
-            [&] { load(0, 1, 1, s, k3); });
+            [&] { load(0, 1, 1, ra, k3, su.kend); });
       wait_barrier<2 * kGroupLoads>();
     }
     // The next unit's slab 0 is in LDS and its slab 1 on the way. Its epilogue inputs, and the
@@ -566,71 +641,29 @@ __global__ __launch_bounds__(256) void splitk_reduce_kernel(const ReduceArgs r) 
   }
 }
 
-// out[c][r] = bf16(f(in[r][c])) for an R x C matrix (row strides ldi, ldo), and optionally
-// out_n[r][c] = bf16(f(in[r][c])) (row stride ldn): 64 x 64 tiles through LDS, every global
-// access row-contiguous (four elements per thread). GRAD: f is grad_value with row r's
-// GradParams (the loss gradient of stored float32 logits), else the identity.
-template <class TI, bool GRAD = false>
-__global__ __launch_bounds__(256) void transpose_kernel(const TransposeArgs t) {
-  __shared__ float tile[64][65];
-  const TI* in = static_cast<const TI*>(t.in);
-  __bf16* out = static_cast<__bf16*>(t.out);
-  __bf16* outn = static_cast<__bf16*>(t.out_n);
-  const int64_t ct = (t.C + 63) / 64;
-  const int64_t r0 = (int64_t)(blockIdx.x / ct) * 64, c0 = (int64_t)(blockIdx.x % ct) * 64;
-  const int q = threadIdx.x & 15, p = threadIdx.x >> 4;  // 16 quads per row, 16 rows per pass
+// G = the loss gradient of stored float32 logits, from each row's GradParams, in bf16 (the
+// kEpiGrad formula): one row and 8 columns per thread. Bound by memory.
+constexpr int kGradCols = 256 * 8;
+__global__ __launch_bounds__(256) void grad_kernel(const GradArgs t) {
+  const int64_t tiles = (t.V + kGradCols - 1) / kGradCols;
+  const int64_t r = blockIdx.x / tiles;
+  const int64_t c = (int64_t)(blockIdx.x - r * tiles) * kGradCols + threadIdx.x * 8;
+  if (c >= t.V) return;
+  const float* z = t.Z + r * t.ldz + c;
+  __bf16* o = t.G + r * t.ldg + c;
+  const GradParams gp = t.gp[r];
+  if (c + 8 <= t.V) {
+    const f32x4 x = __builtin_nontemporal_load((const f32x4*)z);
+    const f32x4 y = __builtin_nontemporal_load((const f32x4*)z + 1);
+    bf16x8 g;
 #pragma unroll
-  for (int pass = 0; pass < 4; ++pass) {
-    const int lr = p + 16 * pass;
-    const int64_t r = r0 + lr, c = c0 + 4 * q;
-    float v[4] = {0.f, 0.f, 0.f, 0.f};
-    if (r < t.R) {
-      const TI* src = in + r * t.ldi + c;
-      if (c + 4 <= t.C) {
-        if constexpr (sizeof(TI) == 4) {
-          const f32x4 x = *(const f32x4*)src;
-          v[0] = x[0], v[1] = x[1], v[2] = x[2], v[3] = x[3];
-        } else {
-          const bf16x4 x = *(const bf16x4*)src;
-          v[0] = (float)x[0], v[1] = (float)x[1], v[2] = (float)x[2], v[3] = (float)x[3];
-        }
-      } else {
-        for (int e = 0; e < 4; ++e)
-          if (c + e < t.C) v[e] = (float)src[e];
-      }
-      if constexpr (GRAD) {
-        const GradParams gp = t.gp[r];
-#pragma unroll
-        for (int e = 0; e < 4; ++e) v[e] = grad_value(gp, v[e], c + e);
-      }
-      if (outn) {
-        __bf16* dst = outn + r * t.ldn + c;
-        if (c + 4 <= t.C) {
-          *(bf16x4*)dst = bf16x4{(__bf16)v[0], (__bf16)v[1], (__bf16)v[2], (__bf16)v[3]};
-        } else {
-          for (int e = 0; e < 4; ++e)
-            if (c + e < t.C) dst[e] = (__bf16)v[e];
-        }
-      }
+    for (int e = 0; e < 4; ++e) {
+      g[e] = (__bf16)grad_value(gp, x[e], c + e);
+      g[4 + e] = (__bf16)grad_value(gp, y[e], c + 4 + e);
     }
-#pragma unroll
-    for (int e = 0; e < 4; ++e) tile[lr][4 * q + e] = v[e];
-  }
-  __syncthreads();
-#pragma unroll
-  for (int pass = 0; pass < 4; ++pass) {
-    const int lc = p + 16 * pass;
-    const int64_t c = c0 + lc, r = r0 + 4 * q;
-    if (c >= t.C) continue;
-    __bf16* dst = out + c * t.ldo + r;
-    const bf16x4 x = {(__bf16)tile[4 * q][lc], (__bf16)tile[4 * q + 1][lc],
-                      (__bf16)tile[4 * q + 2][lc], (__bf16)tile[4 * q + 3][lc]};
-    if (r + 4 <= t.R) {
-      *(bf16x4*)dst = x;
-    } else {
-      for (int e = 0; e < 4; ++e)
-        if (r + e < t.R) dst[e] = x[e];
-    }
+    *(bf16x8*)o = g;
+  } else {
+    for (int e = 0; c + e < t.V; ++e) o[e] = (__bf16)grad_value(gp, z[e], c + e);
   }
 }
 
@@ -676,9 +709,9 @@ hipError_t launch_gemm_epi(GemmArgs g, GemmQueuePool& queues, int num_cu, hipStr
   g.c_split_stride = 0;
   g.c_vec = g.epi == kEpiLseStore && ((uintptr_t)g.C % 16 == 0) && g.ldc % 4 == 0;
   g.units = gemm_tiles(g);
-  const void* fn = g.epi == kEpiLse        ? (const void*)&gemm_bf16_kernel<false, kEpiLse>
-                   : g.epi == kEpiGrad     ? (const void*)&gemm_bf16_kernel<false, kEpiGrad>
-                   : g.epi == kEpiLseStore ? (const void*)&gemm_bf16_kernel<false, kEpiLseStore>
+  const void* fn = g.epi == kEpiLse        ? (const void*)&gemm_bf16_kernel<false, kEpiLse, false, false>
+                   : g.epi == kEpiGrad     ? (const void*)&gemm_bf16_kernel<false, kEpiGrad, false, false>
+                   : g.epi == kEpiLseStore ? (const void*)&gemm_bf16_kernel<false, kEpiLseStore, false, false>
                                            : nullptr;
   if (!fn) return hipErrorInvalidValue;
   return launch_units(g, fn, queues, num_cu, stream);
@@ -704,15 +737,18 @@ int64_t gemm_splitk_count(int64_t M, int64_t N, int64_t K, int64_t max_splits, i
   return best;
 }
 
-hipError_t launch_gemm_nt(GemmArgs g, bool beta, float* partial, int64_t max_splits,
-                          GemmQueuePool& queues, int num_cu, hipStream_t stream) {
+hipError_t launch_gemm(GemmArgs g, bool a_kmajor, bool beta, float* partial, int64_t max_splits,
+                       GemmQueuePool& queues, int num_cu, hipStream_t stream) {
   if (g.M <= 0 || g.N <= 0) return hipSuccess;
-  // A is M x K, B is N x K: the smaller one's tiles run fastest
+  // the smaller dimension's tiles run fastest
   g.m_fastest = g.M <= g.N;
   const int64_t splits = partial ? gemm_splitk_count(g.M, g.N, g.K, max_splits, num_cu) : 1;
   g.units = gemm_tiles(g) * splits;
-  const void* fn = beta && splits <= 1 ? (const void*)&gemm_bf16_kernel<true, kEpiStore>
-                                       : (const void*)&gemm_bf16_kernel<false, kEpiStore>;
+  if (beta && splits <= 1 && !a_kmajor) return hipErrorInvalidValue;   // no such product here
+  const void* fn = !a_kmajor ? (const void*)&gemm_bf16_kernel<false, kEpiStore, false, true>
+                   : beta && splits <= 1
+                       ? (const void*)&gemm_bf16_kernel<true, kEpiStore, true, true>
+                       : (const void*)&gemm_bf16_kernel<false, kEpiStore, true, true>;
   const bool c_aligned = ((uintptr_t)g.C % 16 == 0) && g.ldc % 4 == 0;
   if (splits <= 1) {
     g.k_split = g.K > 0 ? g.K : 1;
@@ -742,16 +778,12 @@ hipError_t launch_gemm_nt(GemmArgs g, bool beta, float* partial, int64_t max_spl
                          stream);
 }
 
-hipError_t launch_transpose(TransposeArgs t, bool in_f32, hipStream_t stream) {
-  if (t.R <= 0 || t.C <= 0) return hipSuccess;
-  if (t.gp && !in_f32) return hipErrorInvalidValue;
-  const int64_t tiles = ((t.C + kTransposeTile - 1) / kTransposeTile) *
-                        ((t.R + kTransposeTile - 1) / kTransposeTile);
-  const void* fn = t.gp    ? (const void*)&transpose_kernel<float, true>
-                   : in_f32 ? (const void*)&transpose_kernel<float>
-                            : (const void*)&transpose_kernel<__bf16>;
-  void* args[] = {&t};
-  return hipLaunchKernel(fn, dim3((unsigned)tiles), dim3(256), args, 0, stream);
+hipError_t launch_grad(const GradArgs& t, hipStream_t stream) {
+  if (t.rows <= 0) return hipSuccess;
+  const int64_t tiles = (t.V + kGradCols - 1) / kGradCols * t.rows;
+  void* args[] = {const_cast<GradArgs*>(&t)};
+  return hipLaunchKernel((const void*)&grad_kernel, dim3((unsigned)tiles), dim3(256), args, 0,
+                         stream);
 }
 
 }  // namespace cis

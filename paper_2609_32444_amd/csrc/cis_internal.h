@@ -84,12 +84,9 @@ constexpr size_t ws_bytes(int64_t T) { return ws_layout(T, 0).total; }
 //   Z   float[rows, ldz]   the chunk's logits (the default backward only)
 //   then per row and 64-column block the pair (max, exp-sum) (float2[rows, ntv]), the sampled
 //   logit (float[rows]) and the gradient parameters (GradParams[rows])
-//   Wt  bf16[H, ldv]       W^T (backward)
-//   Gt  bf16[V, ldc]       (dL/dz)^T of the rows of a dL/dW group (backward)
-//   Ht  bf16[H, ldc]       their hidden states transposed (backward)
-//   Gb  bf16[rows, ldv]    dL/dz of the chunk in bf16 (backward)
+//   G   bf16[grows, ldv]   dL/dz of the rows of a dL/dW group (backward)
 //   P   float[lm_splits, rows, H]  split-K partials of dL/dh (backward)
-// with rows = min(T, chunk), ldc = min(T, lm_dw_rows(chunk)) and row strides rounded up by
+// with rows = min(T, chunk), grows = min(T, lm_dw_rows(chunk)) and row strides rounded up by
 // lm_stride.
 constexpr int64_t kLmMaxH = int64_t(1) << 16;
 constexpr int64_t kLmMaxChunk = int64_t(1) << 16;
@@ -97,10 +94,8 @@ constexpr int64_t kLmMaxChunk = int64_t(1) << 16;
 // stay below 2^23 elements: V (the contracted length of dL/dh) and ld_h, ld_w up to 2^22.
 constexpr int64_t kLmMaxV = int64_t(1) << 22;
 constexpr int64_t kLmMaxLd = int64_t(1) << 22;
-// Row stride of n elements: whole 128-byte lines of bf16, so that neither a transposed tile's
-// 64-element rows nor a product's slabs straddle two, where that adds at most an eighth; else
-// 16-byte chunks. (V = 50257, 1777 rows: G and G^T from the logits took 233 us with rows of
-// whole chunks, see transpose_kernel.)
+// Row stride of n elements: whole 128-byte lines of bf16, so that a product's slab rows do not
+// straddle two, where that adds at most an eighth; else 16-byte chunks.
 inline int64_t lm_stride(int64_t n) { return n >= 512 ? (n + 63) / 64 * 64 : (n + 7) / 8 * 8; }
 // Splits of the contraction of dL/dh that the partial buffer holds: with few tiles, as many as
 // fill 256 compute units (the buffer is then at most 64 MiB).
@@ -109,8 +104,8 @@ inline int64_t lm_splits(int64_t rows, int64_t H) {
   return tiles >= 32 ? 8 : (tiles <= 8 ? 32 : 256 / tiles);
 }
 // dL/dW is one product per group of consecutive chunks, up to kLmDwRows rows: fewer products
-// that accumulate into dL/dW. A group holds whole chunks; the chunk's columns of Gt and Ht start
-// 16-byte aligned only when chunk is a multiple of 8, otherwise a group is one chunk.
+// that accumulate into dL/dW. A group holds whole chunks when chunk is a multiple of 8, otherwise
+// it is one chunk (cis_lmhead_loss_bwd states the groups).
 constexpr int64_t kLmDwRows = int64_t(1) << 14;
 inline int64_t lm_dw_rows(int64_t chunk) {
   if (chunk % 8 != 0 || chunk >= kLmDwRows) return chunk;
@@ -118,8 +113,8 @@ inline int64_t lm_dw_rows(int64_t chunk) {
 }
 struct LmLayout {
   WsLayout loss;
-  int64_t ldz, ldv, ldc, ntv, splits;
-  size_t z, wt, gt, ht, gb, part, queue, total;
+  int64_t ldz, ldv, ntv, splits;
+  size_t z, g, part, queue, total;
   size_t tpart, tzy, tgp;  // the product's (max, exp-sum) pairs, sampled logits, gradient
                            // parameters of the chunk's rows
   bool fused;
@@ -135,7 +130,6 @@ inline LmLayout lm_layout(int64_t T, int64_t V, int64_t H, int64_t chunk, int64_
   M.ldv = M.ldz;
   M.ntv = (V + 255) / 256 * 4;  // four 64-column blocks per 256-column tile
   const int64_t grows = T < lm_dw_rows(chunk) ? T : lm_dw_rows(chunk);
-  M.ldc = lm_stride(grows > 0 ? grows : 1);
   M.queue = align_up(M.loss.total, 256);  // the products' work queues
   M.z = M.queue + 256;
   size_t end = M.z;
@@ -146,15 +140,9 @@ inline LmLayout lm_layout(int64_t T, int64_t V, int64_t H, int64_t chunk, int64_
   end += align_up((size_t)rows * 4, 256);
   M.tgp = end;
   end += align_up((size_t)rows * sizeof(GradParams), 256);
-  M.wt = M.gt = M.ht = M.gb = M.part = end;
+  M.g = M.part = end;
   if (bwd) {
-    end += align_up((size_t)H * (size_t)M.ldv * 2, 256);
-    M.gt = end;
-    end += align_up((size_t)V * (size_t)M.ldc * 2, 256);
-    M.ht = end;
-    end += align_up((size_t)H * (size_t)M.ldc * 2, 256);
-    M.gb = end;
-    end += align_up((size_t)rows * (size_t)M.ldv * 2, 256);
+    end += align_up((size_t)grows * (size_t)M.ldv * 2, 256);
     M.part = end;
     M.splits = rows > 0 ? lm_splits(rows, H) : 1;
     end += align_up((size_t)M.splits * (size_t)rows * (size_t)H * 4, 256);
