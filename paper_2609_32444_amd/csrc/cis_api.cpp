@@ -300,8 +300,8 @@ int launch_rows(const LossCall& c, const Ws& ws, bool clear_queue, int dev,
   const int64_t rows = c.T;
   cis::RowArgs ra = row_args(c, ws, c.logits, c.dlogits, c.ld, c.ld_g, 0, rows);
   const int32_t nvec = ra.nvec;
-  const cis::RowVariant& var = c.ext ? cis::select_row_variant_ext(c.dtype, c.bwd, nvec)
-                                     : cis::select_row_variant(c.dtype, c.bwd, nvec);
+  const cis::RowVariant* var = c.ext ? &cis::select_row_variant_ext(c.dtype, c.bwd, nvec)
+                                     : &cis::select_row_variant(c.dtype, c.bwd, nvec);
   // forward pass over long rows: segment kernel + combine (when the workspace has the room)
   const cis::SegVariant* sv =
       (!c.bwd && ws.L.seg) ? cis::select_seg_variant(c.dtype, nvec) : nullptr;
@@ -321,19 +321,26 @@ int launch_rows(const LossCall& c, const Ws& ws, bool clear_queue, int dev,
       return CIS_ERR_LAUNCH;
     return launch_combine(c, ra, sa, rows, stream);
   }
-  const int per_cu = blocks_per_cu(var.fn, var.block, dev);
-  const int64_t resident = (int64_t)per_cu * info.num_cu;
+  int64_t resident = (int64_t)blocks_per_cu(var->fn, var->block, dev) * info.num_cu;
+  if (c.bwd && rows > info.num_cu && rows <= cis::few_rounds(nvec) * resident) {
+    const cis::RowVariant* few = c.ext ? cis::select_row_variant_few_ext(c.dtype, nvec)
+                                       : cis::select_row_variant_few(c.dtype, nvec);
+    if (few) {
+      var = few;
+      resident = (int64_t)blocks_per_cu(var->fn, var->block, dev) * info.num_cu;
+    }
+  }
   const int grid = (int)(rows < resident ? rows : resident);
   // the fused pass takes its rows from a queue, except one-wave rows and a workgroup's first
   // three (see cis_row_kernel)
-  if (!c.bwd || var.block <= 64 || rows <= 3 * (int64_t)grid) ra.queue = nullptr;
+  if (!c.bwd || var->block <= 64 || rows <= 3 * (int64_t)grid) ra.queue = nullptr;
   if (ra.queue && clear_queue) {
     void* qargs[] = {&ra.queue};
     if (hipLaunchKernel(cis::queue_reset_kernel(), dim3(1), dim3(64), qargs, 0, stream) !=
         hipSuccess)
       return CIS_ERR_LAUNCH;
   }
-  return launch(var.fn, grid, var.block, &ra, stream);
+  return launch(var->fn, grid, var->block, &ra, stream);
 }
 
 // The call's statistics and loss. Few rows by one workgroup; more by one per part and another

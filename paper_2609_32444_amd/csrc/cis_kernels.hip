@@ -79,6 +79,13 @@ static const RowVariant kBf16Fwd[] = CIS_FWD_TABLE(Bf16, 18);
 static const RowVariant kF32Bwd[] = CIS_BWD_TABLE(F32);
 static const RowVariant kF32Fwd[] = CIS_FWD_TABLE(F32, 15);
 
+static const RowVariant kBf16Few[] = CIS_FEW_TABLE(Bf16);
+static const RowVariant kF32Few[] = CIS_FEW_TABLE(F32);
+const RowVariant* select_row_variant_few(int dtype, int32_t nvec) {
+  if (nvec <= kFewMinVec || nvec > kFewMaxVec) return nullptr;
+  return &pick_variant(dtype == CIS_BF16 ? kBf16Few : kF32Few, 3, nvec);
+}
+
 const RowVariant& select_row_variant(int dtype, bool bwd, int32_t nvec) {
   constexpr int nb = sizeof(kBf16Bwd) / sizeof(kBf16Bwd[0]);
   constexpr int nf = sizeof(kBf16Fwd) / sizeof(kBf16Fwd[0]);

@@ -12,6 +12,13 @@ static const RowVariant kBf16BwdExt[] = CIS_BWD_TABLE(Bf16);
 static const RowVariant kBf16FwdExt[] = CIS_FWD_TABLE(Bf16, 18);
 static const RowVariant kF32BwdExt[] = CIS_BWD_TABLE(F32);
 static const RowVariant kF32FwdExt[] = CIS_FWD_TABLE(F32, 15);
+static const RowVariant kBf16FewExt[] = CIS_FEW_TABLE(Bf16);
+static const RowVariant kF32FewExt[] = CIS_FEW_TABLE(F32);
+const RowVariant* select_row_variant_few_ext(int dtype, int32_t nvec) {
+  if (nvec <= kFewMinVec || nvec > kFewMaxVec) return nullptr;
+  return &pick_variant(dtype == CIS_BF16 ? kBf16FewExt : kF32FewExt, 3, nvec);
+}
+
 const RowVariant& select_row_variant_ext(int dtype, bool bwd, int32_t nvec) {
   constexpr int nb = sizeof(kBf16BwdExt) / sizeof(kBf16BwdExt[0]);
   constexpr int nf = sizeof(kBf16FwdExt) / sizeof(kBf16FwdExt[0]);

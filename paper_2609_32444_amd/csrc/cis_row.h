@@ -1166,6 +1166,14 @@ __global__ __launch_bounds__(BLOCK) void cis_row_kernel(const RowArgs a) {
    CIS_V(E, 1024, 7, 0, true, false),  CIS_V(E, 1024, 11, 0, true, false),                  \
    CIS_V(E, 1024, 15, 0, true, false), CIS_V(E, 1024, 18, 0, true, false),                  \
    CIS_V(E, 1024, 18, 9, true, false)}
+// Fused calls of at most kFewRounds rows per resident workgroup of that ladder: smaller blocks, so
+// that more rows are in flight per compute unit and the last round costs less. bf16, ladder and
+// these, us per call: V = 16384, 3001 rows 48.5 and 41.4, 4096 rows (5.3 rounds) 61.2 and 63.0;
+// V = 32768, 1024 rows 36.8 and 26.3, 16384 rows 397 and 427; V = 50257, 1024 rows 51.5 and 44.4
+// (512 x 13), 3001 rows 127 and 127, 16384 rows 598 and 677.
+#define CIS_FEW_TABLE(E)                                                                    \
+  {CIS_V(E, 256, 7, 0, true, false), CIS_V(E, 256, 15, 0, true, false),                     \
+   CIS_V(E, 512, 15, 0, true, false)}
 #define CIS_FWD_TABLE(E, LAST)                                                              \
   {CIS_V(E, 64, 1, 0, false, true),    CIS_V(E, 64, 3, 0, false, true),                     \
    CIS_V(E, 64, 7, 0, false, true),    CIS_V(E, 64, 15, 0, false, true),                    \
@@ -1173,6 +1181,8 @@ __global__ __launch_bounds__(BLOCK) void cis_row_kernel(const RowArgs a) {
    CIS_V(E, 512, 15, 0, false, true),  CIS_V(E, 1024, 11, 0, false, true),                  \
    CIS_V(E, 1024, LAST, 0, false, true)}
 
+
+constexpr int32_t kFewMinVec = 1024, kFewMaxVec = 8192;   // longer than one wave's rows
 
 // First variant whose row capacity holds `nvec` vectors, else the last (which streams the rest).
 inline const RowVariant& pick_variant(const RowVariant* t, int n, int32_t nvec) {

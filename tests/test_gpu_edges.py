@@ -104,6 +104,22 @@ def test_fixed_rows_and_statistics_parts(V, T):
     test_row_queue_and_stale_workspace(V, T)
 
 
+# Calls of a few rows per workgroup take smaller blocks (CIS_FEW_TABLE; test_bf16_vocab_sizes and
+# test_f32_vocab_sizes are such calls): the ladder's own variants with more rows than that, at and
+# just past their capacities, and the smaller blocks at theirs.
+@pytest.mark.parametrize("V,T,dtype", [
+    (8193, 4000, torch.bfloat16), (16384, 4000, torch.bfloat16), (16385, 2200, torch.bfloat16),
+    (32768, 2200, torch.bfloat16), (32769, 2200, torch.bfloat16), (65530, 1300, torch.bfloat16),
+    (4097, 4000, torch.float32), (16380, 2200, torch.float32), (8193, 700, torch.bfloat16),
+    (16385, 700, torch.bfloat16), (32768, 700, torch.bfloat16), (32769, 260, torch.bfloat16),
+    (65536, 260, torch.bfloat16)])
+def test_blocks_by_row_count(V, T, dtype):
+    epv = 8 if dtype == torch.bfloat16 else 4
+    b = make_random_batch(T, V, dtype, DEV, seed=V % 83, ld=((V + epv - 1) // epv) * epv,
+                          mask_p=0.5)
+    run_and_check(b)
+
+
 # The row kernel's long-row variants, at and just past their capacities, with more rows than the
 # pass over segments takes (test_bf16_vocab_sizes and test_f32_vocab_sizes have fewer).
 @pytest.mark.parametrize("V,dtype", [(V, torch.bfloat16) for V in
