@@ -323,7 +323,9 @@ const void* finalize_kernel(int block, bool parts);
 // The fused variant for calls of few rows per workgroup of the variant above that the chip holds at
 // once (at most few_rounds, and more than one row per CU), or null where there is none (see
 // CIS_FEW_TABLE).
-inline int64_t few_rounds(int32_t nvec) { return nvec > 4096 ? 6 : (nvec > 2048 ? 12 : 4); }
+inline int64_t few_rounds(int32_t nvec) {
+  return nvec > 4096 ? 6 : nvec > 3584 ? 16 : nvec > 2048 ? 0 : 4;
+}
 const RowVariant* select_row_variant_few(int dtype, int32_t nvec);
 const RowVariant* select_row_variant_few_ext(int dtype, int32_t nvec);
 

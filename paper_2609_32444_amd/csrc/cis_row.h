@@ -1159,18 +1159,30 @@ __global__ __launch_bounds__(BLOCK) void cis_row_kernel(const RowArgs a) {
 // bf16) 1024 x 3 without the prefetch took over once loads were issued in slot order and the
 // queue tickets were drawn ahead of the stores: 0.625 ms against 0.635 for 512 x 7 without and
 // 0.657 with the prefetch, 0.658 for 256 x 15 with it and 0.677 without.
+// Steps between the sizes of that choice: a workgroup that holds twice the row's vectors leaves
+// half of its loads and stores out of range and fits the compute unit half as often. bf16, 16384
+// rows, us before and after: V = 4600 71.2 and 65.3 (64 x 9); 20000 / 24000 / 28000 326 / 344 / 383
+// and 254 / 299 / 358 (512 x 4, 5, 6 in place of 1024 x 3); 36000 / 44000 478 / 531 and 435 / 518
+// (1024 x 4, 5 in place of 7); 80000 887 and 873 (1024 x 9). Steps that gave under 2.5% (64 x 2,
+// 64 x 13, 512 x 2, 1024 x 6, 1024 x 13) are left out.
 #define CIS_BWD_TABLE(E)                                                                    \
   {CIS_V(E, 64, 1, 0, true, true),     CIS_V(E, 64, 3, 0, true, true),                      \
-   CIS_V(E, 64, 7, 0, true, true),     CIS_V(E, 64, 15, 0, true, true),                     \
-   CIS_V(E, 512, 3, 0, true, false),   CIS_V(E, 1024, 3, 0, true, false),                   \
-   CIS_V(E, 1024, 7, 0, true, false),  CIS_V(E, 1024, 11, 0, true, false),                  \
-   CIS_V(E, 1024, 15, 0, true, false), CIS_V(E, 1024, 18, 0, true, false),                  \
-   CIS_V(E, 1024, 18, 9, true, false)}
-// Fused calls of at most kFewRounds rows per resident workgroup of that ladder: smaller blocks, so
+   CIS_V(E, 64, 5, 0, true, true),     CIS_V(E, 64, 7, 0, true, true),                      \
+   CIS_V(E, 64, 9, 0, true, true),     CIS_V(E, 64, 11, 0, true, true),                     \
+   CIS_V(E, 64, 15, 0, true, true),    CIS_V(E, 512, 3, 0, true, false),                    \
+   CIS_V(E, 512, 4, 0, true, false),   CIS_V(E, 512, 5, 0, true, false),                    \
+   CIS_V(E, 512, 6, 0, true, false),   CIS_V(E, 1024, 3, 0, true, false),                   \
+   CIS_V(E, 1024, 4, 0, true, false),  CIS_V(E, 1024, 5, 0, true, false),                   \
+   CIS_V(E, 1024, 7, 0, true, false),  CIS_V(E, 1024, 9, 0, true, false),                   \
+   CIS_V(E, 1024, 11, 0, true, false), CIS_V(E, 1024, 15, 0, true, false),                  \
+   CIS_V(E, 1024, 18, 0, true, false), CIS_V(E, 1024, 18, 9, true, false)}
+// Fused calls of at most few_rounds() rows per resident workgroup of that ladder: smaller blocks, so
 // that more rows are in flight per compute unit and the last round costs less. bf16, ladder and
 // these, us per call: V = 16384, 3001 rows 48.5 and 41.4, 4096 rows (5.3 rounds) 61.2 and 63.0;
-// V = 32768, 1024 rows 36.8 and 26.3, 16384 rows 397 and 427; V = 50257, 1024 rows 51.5 and 44.4
-// (512 x 13), 3001 rows 127 and 127, 16384 rows 598 and 677.
+// V = 32768, 1024 rows 36.8 and 26.3, 4096 rows (16 rounds) 116.3 and 114.9, 8192 rows 210 and 218;
+// V = 36000, 1024 rows 40.4 and 33.4; V = 50257, 1024 rows 51.5 and 44.4 (512 x 13), 3001 rows 127
+// and 127, 16384 rows 598 and 677. Between 2049 and 3584 vectors the ladder's own blocks are the
+// better ones at every count (V = 20000, 1024 rows 17.5 against 19.6).
 #define CIS_FEW_TABLE(E)                                                                    \
   {CIS_V(E, 256, 7, 0, true, false), CIS_V(E, 256, 15, 0, true, false),                     \
    CIS_V(E, 512, 15, 0, true, false)}

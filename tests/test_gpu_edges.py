@@ -112,6 +112,12 @@ def test_fixed_rows_and_statistics_parts(V, T):
     (32768, 2200, torch.bfloat16), (32769, 2200, torch.bfloat16), (65530, 1300, torch.bfloat16),
     (4097, 4000, torch.float32), (16380, 2200, torch.float32), (8193, 700, torch.bfloat16),
     (16385, 700, torch.bfloat16), (32768, 700, torch.bfloat16), (32769, 260, torch.bfloat16),
+    (3072, 300, torch.bfloat16), (3073, 300, torch.bfloat16), (5120, 300, torch.bfloat16),
+    (5121, 300, torch.bfloat16), (6145, 300, torch.bfloat16), (20480, 700, torch.bfloat16),
+    (20481, 700, torch.bfloat16), (24577, 700, torch.bfloat16), (28672, 700, torch.bfloat16),
+    (28673, 700, torch.bfloat16), (28673, 4200, torch.bfloat16), (40960, 1600, torch.bfloat16),
+    (40961, 1600, torch.bfloat16), (49153, 1600, torch.bfloat16), (81920, 300, torch.bfloat16),
+    (81921, 300, torch.bfloat16), (10241, 700, torch.float32), (24575, 1600, torch.float32),
     (65536, 260, torch.bfloat16)])
 def test_blocks_by_row_count(V, T, dtype):
     epv = 8 if dtype == torch.bfloat16 else 4
