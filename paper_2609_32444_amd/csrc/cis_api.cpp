@@ -309,6 +309,7 @@ int launch_rows(const LossCall& c, const Ws& ws, bool clear_queue, int dev,
     cis::SegArgs sa{};
     sa.segvec = sv->block * sv->k;
     sa.nseg = (int32_t)((nvec + sa.segvec - 1) / sa.segvec);
+    sa.rot = cis::seg_rotation(sa.nseg, sa.segvec, nvec);
     sa.part = reinterpret_cast<float2*>(ws.base + ws.L.part);
     sa.zy = ws.f(ws.L.zy);
     sa.stride = cis::kSegMax;

@@ -206,7 +206,16 @@ struct SegArgs {
   int64_t stride;   // pieces per row in `part`
   GradParams* gp;   // [T] nullable: gradient parameters for the fused LM-head pass
   uint32_t* done;   // nullable: rows whose outputs are stored (the fused pass over few rows)
+  int32_t rot;      // seg_rotation() (split forward pass)
 };
+// Workgroup b runs on XCD b % 8, so the segment at a given place of the row meets the same XCD again
+// after 8 / gcd(nseg, 8) rows: one more place of rotation from then on. None (-1) for an odd nseg,
+// which visits every XCD by itself, and for equal segments: there the plain order is the faster one
+// (16384 rows of V = 151936 782 us against 798, V = 32768 171 against 178).
+inline int32_t seg_rotation(int32_t nseg, int32_t segvec, int32_t nvec) {
+  if (nseg % 2 != 0 || nvec % segvec == 0) return -1;
+  return nseg % 8 == 0 ? 0 : nseg % 4 == 0 ? 1 : 2;
+}
 constexpr int kCombineBlock = 256;
 constexpr int kSegGradBlock = 128, kSegGradK = 8;   // 16 KiB of logits per workgroup
 // A compiled segment kernel: `block` threads with K 16-byte vectors each, so block * K vectors

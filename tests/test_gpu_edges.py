@@ -37,8 +37,8 @@ def run_and_check(b, bwd=True, report=None, **kw):
 
 # V values chosen to hit every row-kernel variant of both element types, ragged last vectors
 # (V % 8 != 0), single partial vectors, and rows longer than the register-resident capacity.
-# Fused-pass row capacities in 16-byte vectors: 128, 256, 512, 1024, 2048, 4096, 8192, 12288,
-# 16384, 19456 in registers, then 27648 with LDS (bf16: 8 logits per vector, fp32: 4); longer
+# Fused-pass row capacities in 16-byte vectors: 128, 256, 384, 512, 640, 768, 1024, 2048, 2560, 3072,
+# 3584, 4096, 5120, 6144, 8192, 10240, 12288, 16384, 19456 in registers, then 27648 with LDS (bf16: 8 logits per vector, fp32: 4); longer
 # rows stream the rest. The lists put rows in every variant, at and just past capacities.
 BF16_VS = [1, 2, 7, 8, 9, 1000, 1001, 2048, 2049, 4097, 8192, 12000, 16384, 30000, 32768,
            40961, 65536, 90001, 100000, 130001, 151936, 155648, 155649, 160000, 200000, 200003,
@@ -136,6 +136,19 @@ def test_row_kernel_long_rows(V, dtype):
     b = make_random_batch(200, V, dtype, DEV, seed=V % 89, ld=((V + epv - 1) // epv) * epv,
                           mask_p=0.3)
     run_and_check(b)
+
+
+# The split forward pass with its segments rotated over the XCDs (2, 4, 6, 8 and 16 segments, the last
+# one short) and not (odd counts, equal segments), over more rows than a rotation takes to come back.
+@pytest.mark.parametrize("V,dtype", [(16400, torch.bfloat16), (28001, torch.bfloat16),
+                                     (44000, torch.bfloat16), (64000, torch.bfloat16),
+                                     (128256, torch.bfloat16), (32768, torch.bfloat16),
+                                     (50257, torch.bfloat16), (14001, torch.float32)])
+def test_segment_rotation(V, dtype):
+    epv = 8 if dtype == torch.bfloat16 else 4
+    b = make_random_batch(150, V, dtype, DEV, seed=V % 79, ld=((V + epv - 1) // epv) * epv,
+                          mask_p=0.7)
+    run_and_check(b, bwd=False)
 
 
 # Few long rows: the fused pass over segments (cis_seg_grad_kernel), at the first and last row
