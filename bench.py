@@ -101,7 +101,8 @@ def lmhead_traffic():
         return None
 
 
-LMHEAD_SOURCES = ("paper_2609_32444_amd/csrc/cis_gemm.hip", "paper_2609_32444_amd/csrc/cis_gemm.h")
+LMHEAD_SOURCES = ("paper_2609_32444_amd/csrc/cis_gemm.hip", "paper_2609_32444_amd/csrc/cis_gemm.h",
+                  "paper_2609_32444_amd/csrc/cis_plan.h")
 
 
 PROBE_MAX_ROW_BYTES = 19 * 1024 * 16   # the row-pattern probes hold one row per workgroup

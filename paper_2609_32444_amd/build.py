@@ -20,6 +20,7 @@ PROBE_PATH = os.path.join(HERE, "libcis_probe.so")
 PROBE_SOURCES = [os.path.join(HERE, "csrc", "bw_probe.hip")]
 HEADERS = [os.path.join(ROOT, "include", "cis.h"), os.path.join(HERE, "csrc", "cis_internal.h"),
            os.path.join(HERE, "csrc", "cis_row.h"), os.path.join(HERE, "csrc", "cis_gemm.h"),
+           os.path.join(HERE, "csrc", "cis_plan.h"),
            os.path.join(HERE, "csrc", "cis_seg.h"), os.path.join(HERE, "csrc", "cis_stats.h")]
 
 # -packed-fp32-ops: no v_pk_{add,mul,fma}_f32 in device code (the compiler's host pass warns

@@ -5,6 +5,7 @@
 #include <stdint.h>
 
 #include "cis_internal.h"
+#include "cis_plan.h"
 
 namespace cis {
 
@@ -74,8 +75,6 @@ struct GradArgs {
   int64_t rows, V, ldz, ldg;
 };
 
-constexpr int kGemmTile = 256;      // C tile per workgroup (rows and columns)
-constexpr int kGemmBK = 64;         // contraction slab
 constexpr int kGemmWaveM = 128;     // C tile per wave: 128 rows x 64 columns (8 waves)
 constexpr int kGemmWaveN = 64;
 constexpr int kGemmQueues = 8;      // one work queue per XCD

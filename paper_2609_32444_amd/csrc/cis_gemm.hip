@@ -319,16 +319,14 @@ __device__ __forceinline__ UnitSrc unit_src(const GemmArgs& g, int u) {
   return s;
 }
 
-// The unit's operands at row k of the contraction. A k-major operand's resource starts at that row
-// and ends with the contraction's last one, so rows at or past kend read as zero; columns past the
-// matrix are read where they lie within it (they reach only results that are not stored).
-// (Formed right before an operand's loads, with 32-bit arithmetic where it can be: scalar
+// A k-major operand's resource starts at row k of the contraction and ends with its last one
+// (slab_bytes), so rows at or past the end read as zero, and nothing past the matrix is read;
+// columns past the matrix are read where they lie within it (they reach only results that are not
+// stored). (Formed right before an operand's loads, with 32-bit arithmetic where it can be: scalar
 // instructions ahead of the first phase held both waves of a SIMD up, 8% of the product.)
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t slab_rsrc(const __bf16* p, uint32_t cols,
                                                             uint32_t ld, uint32_t k, int left) {
-  const uint32_t last = ((uint32_t)(left - 1) * ld + ((cols + 7) & ~7u)) * 2;   // left <= 64
-  const uint32_t n = left > kGemmBK ? kOobBase : last;
-  return make_rsrc((const char*)p + (uint64_t)k * (uint64_t)(ld * 2), left <= 0 ? 0 : n);
+  return make_rsrc((const char*)p + (uint64_t)k * (uint64_t)(ld * 2), slab_bytes(cols, ld, left));
 }
 
 // The products. A workgroup works through units (tiles, or a tile's share of a split

@@ -285,6 +285,16 @@ def test_lmhead_contraction_tails(H):
     run_case(f"tail_H{H}", b, chunk=69)
 
 
+@pytest.mark.parametrize("T,V,H,chunk", [(256, 300, 8, 191), (130, 65, 8, 65), (130, 65, 120, 65),
+                                         (71, 1025, 64, 69)])
+def test_lmhead_narrow_operands(T, V, H, chunk):
+    """Heads narrower than a tile whose contractions end a row after a slab (V = 65 and 1025 in
+    dL/dh, a last group of 65 rows in dL/dW): a slab's loads reach into the rows after its own,
+    but not past the last one."""
+    b = make_lmhead_batch(T, V, H, device=DEV, seed=19, min_len=8, max_len=40, ld_h=H, ld_w=H)
+    run_case(f"narrow_V{V}_H{H}", b, chunk=chunk)
+
+
 def test_lmhead_queued_products_straddling_chunk():
     """More tiles than CUs with a contraction that ends inside a 16-byte chunk: every tile after
     a workgroup's first has its last slab cleared while the tile before it is multiplied."""

@@ -1,0 +1,61 @@
+"""Bounds that the kernels take from csrc/cis_plan.h, checked on the host over their whole range (the
+header is plain C++: it is compiled here with the host compiler)."""
+
+import ctypes
+import os
+import shutil
+import subprocess
+
+import numpy as np
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+CSRC = os.path.join(ROOT, "paper_2609_32444_amd", "csrc")
+
+SOURCE = """
+#include "cis_plan.h"
+extern "C" {
+uint32_t slab_bytes(uint32_t cols, uint32_t ld, int left) { return cis::slab_bytes(cols, ld, left); }
+}
+"""
+
+
+@pytest.fixture(scope="module")
+def plan(tmp_path_factory):
+    cxx = shutil.which("g++") or shutil.which("clang++") or shutil.which("hipcc")
+    d = tmp_path_factory.mktemp("plan")
+    (d / "plan.cpp").write_text(SOURCE)
+    subprocess.run([cxx, "-std=c++20", "-shared", "-fPIC", "-I", CSRC, str(d / "plan.cpp"), "-o",
+                    str(d / "plan.so")], check=True)
+    lib = ctypes.CDLL(str(d / "plan.so"))
+    lib.slab_bytes.argtypes = [ctypes.c_uint32, ctypes.c_uint32, ctypes.c_int]
+    lib.slab_bytes.restype = ctypes.c_uint32
+    return lib
+
+
+# Offsets (bytes) of the 16-byte loads of one slab of a k-major operand: 64 rows, 256 columns.
+ROWS, COLS = np.divmod(np.arange(64 * 32), 32)
+COLS = COLS * 8
+
+
+@pytest.mark.parametrize("ld", [*range(8, 257, 8), 320, 520, 4096, 1 << 16, 1 << 22])
+def test_slab_loads_stay_in_the_matrix(plan, ld):
+    """With `left` rows of the contraction and `cols` columns from the tile's first one on, the
+    matrix ends at ((left - 1) ld + cols rounded up to 8) elements: no load that the resource lets
+    through ends later, every chunk that holds an element of the slab is let through, and every
+    row past the contraction is not."""
+    off = (ROWS.astype(np.int64) * ld + COLS) * 2
+    for cols in sorted({1, 7, 8, 9, ld // 2, ld - 7, ld - 1, ld} & set(range(1, ld + 1))):
+        cols8 = (cols + 7) // 8 * 8
+        for left in (*range(1, 131), 1000, 1 << 22):
+            n = plan.slab_bytes(cols, ld, left)
+            read = off + 16 <= n
+            assert n % 16 == 0 and n < 1 << 31
+            assert np.all(off[read] + 16 <= ((left - 1) * ld + cols8) * 2), (cols, left)
+            assert np.all(read[(ROWS < left) & (COLS < cols8)]), (cols, left)
+            assert not np.any(read[ROWS >= left]), (cols, left)
+
+
+def test_no_slab_beyond_the_contraction(plan):
+    for left in (0, -1, -64, -1000):
+        assert plan.slab_bytes(8, 8, left) == 0
