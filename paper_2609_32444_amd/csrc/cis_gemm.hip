@@ -47,7 +47,6 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t make_rsrc(const void* base, ui
 // into an unmapped page), clamped to kOobBase: the offsets of a tile's 256 rows stay below it
 // (ld <= 2^22), and kOobBase plus any row offset lies beyond every resource. Rows past R lie
 // beyond theirs. A load beyond its resource returns zeros.
-constexpr uint32_t kOobBase = 0x80000000u;
 __device__ __forceinline__ uint32_t span_bytes(int64_t R, int64_t r0, int64_t K, int64_t ld) {
   if (r0 >= R) return 0;
   const int64_t b = ((R - r0 - 1) * ld + (K + 7) / 8 * 8) * 2;

@@ -50,7 +50,7 @@ def test_slab_loads_stay_in_the_matrix(plan, ld):
         for left in (*range(1, 131), 1000, 1 << 22):
             n = plan.slab_bytes(cols, ld, left)
             read = off + 16 <= n
-            assert n % 16 == 0 and n < 1 << 31
+            assert n % 16 == 0 and n <= 1 << 31
             assert np.all(off[read] + 16 <= ((left - 1) * ld + cols8) * 2), (cols, left)
             assert np.all(read[(ROWS < left) & (COLS < cols8)]), (cols, left)
             assert not np.any(read[ROWS >= left]), (cols, left)
