@@ -640,9 +640,8 @@ __global__ __launch_bounds__(256) void splitk_reduce_kernel(const ReduceArgs r) 
 
 // G = the loss gradient of stored float32 logits, from each row's GradParams, in bf16 (the
 // kEpiGrad formula): one row and 8 columns per thread. Bound by memory.
-constexpr int kGradCols = 256 * 8;
-__global__ __launch_bounds__(256) void grad_kernel(const GradArgs t) {
-  const int64_t tiles = (t.V + kGradCols - 1) / kGradCols;
+__global__ __launch_bounds__(kGradThreads) void grad_kernel(const GradArgs t) {
+  const int64_t tiles = grad_tiles(t.V);
   const int64_t r = blockIdx.x / tiles;
   const int64_t c = (int64_t)(blockIdx.x - r * tiles) * kGradCols + threadIdx.x * 8;
   if (c >= t.V) return;
@@ -776,11 +775,19 @@ hipError_t launch_gemm(GemmArgs g, bool a_kmajor, bool beta, float* partial, int
 }
 
 hipError_t launch_grad(const GradArgs& t, hipStream_t stream) {
-  if (t.rows <= 0) return hipSuccess;
-  const int64_t tiles = (t.V + kGradCols - 1) / kGradCols * t.rows;
-  void* args[] = {const_cast<GradArgs*>(&t)};
-  return hipLaunchKernel((const void*)&grad_kernel, dim3((unsigned)tiles), dim3(256), args, 0,
-                         stream);
+  GradArgs part = t;
+  for (int64_t r0 = 0; r0 < t.rows; r0 += part.rows) {
+    part.rows = grad_rows(t.rows - r0, t.V);
+    part.Z = t.Z + r0 * t.ldz;
+    part.G = t.G + r0 * t.ldg;
+    part.gp = t.gp + r0;
+    void* args[] = {&part};
+    if (hipError_t e = hipLaunchKernel((const void*)&grad_kernel,
+                                       dim3((unsigned)(grad_tiles(t.V) * part.rows)),
+                                       dim3(kGradThreads), args, 0, stream))
+      return e;
+  }
+  return hipSuccess;
 }
 
 }  // namespace cis

@@ -23,4 +23,15 @@ constexpr uint32_t slab_bytes(uint32_t cols, uint32_t ld, int left) {
   return left <= 0 ? 0u : left > reach ? kOobBase : last;
 }
 
+// grad_kernel: a workgroup of kGradThreads takes kGradCols columns of a row. Rows per launch: HIP
+// refuses a launch of 2^32 work items, which 8192 rows of 2^22 columns reach.
+constexpr int kGradThreads = 256;
+constexpr int kGradCols = kGradThreads * 8;
+constexpr int64_t kGradMaxBlocks = int64_t(1) << 20;
+constexpr int64_t grad_tiles(int64_t V) { return (V + kGradCols - 1) / kGradCols; }
+constexpr int64_t grad_rows(int64_t rows, int64_t V) {
+  const int64_t most = kGradMaxBlocks / grad_tiles(V);   // V <= 2^22: at least 512
+  return rows < most ? rows : most;
+}
+
 }  // namespace cis

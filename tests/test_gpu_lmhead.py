@@ -313,6 +313,26 @@ def test_lmhead_largest_vocabulary(recompute):
     run_case("max_vocab", b, chunk=64, recompute=recompute)
 
 
+def test_lmhead_gradient_pass_in_two_launches():
+    """520 rows of 2^22 columns in one chunk are more than a launch of grad_kernel takes (512), in
+    five chunks they are fewer. dL/dW is one group either way, the same product of the
+    same G: bit-equal where every row's G is."""
+    T, V, H = 520, 1 << 22, 8
+    g = torch.Generator(device=DEV).manual_seed(31)
+    h = torch.randn(T, H, generator=g, device=DEV).bfloat16()
+    w = torch.randn(V, H, generator=g, device=DEV).bfloat16()
+    ids = torch.randint(0, V, (T,), generator=g, device=DEV)
+    adv = torch.randn(T, generator=g, device=DEV)
+    lq = torch.full((T,), -16.0, device=DEV)
+    prm, _ = make_params(X.OP_CIS, dict(lam=2.0, kappa=5e-3), -1.0 / T)
+    one, five = (cis.lmhead_loss_bwd(h, w, ids, lq, adv, None, params=prm, chunk=c)
+                 for c in (520, 104))
+    torch.cuda.synchronize()
+    assert one["dweight"].abs().max() > 0
+    for k in ("logp_train", "w", "terms", "loss", "dweight"):
+        assert torch.equal(one[k], five[k]), k
+
+
 def test_lmhead_largest_chunk():
     """chunk = 2^16, the largest the LM-head calls accept, over a batch of exactly that many
     rows: one logits product of 65536 rows and one dL/dW group of K = 65536, against the

@@ -16,6 +16,8 @@ SOURCE = """
 #include "cis_plan.h"
 extern "C" {
 uint32_t slab_bytes(uint32_t cols, uint32_t ld, int left) { return cis::slab_bytes(cols, ld, left); }
+int64_t grad_rows(int64_t rows, int64_t V) { return cis::grad_rows(rows, V); }
+int64_t grad_threads(int64_t V) { return cis::grad_tiles(V) * cis::kGradThreads; }
 }
 """
 
@@ -30,6 +32,9 @@ def plan(tmp_path_factory):
     lib = ctypes.CDLL(str(d / "plan.so"))
     lib.slab_bytes.argtypes = [ctypes.c_uint32, ctypes.c_uint32, ctypes.c_int]
     lib.slab_bytes.restype = ctypes.c_uint32
+    lib.grad_rows.argtypes = [ctypes.c_int64, ctypes.c_int64]
+    lib.grad_threads.argtypes = [ctypes.c_int64]
+    lib.grad_rows.restype = lib.grad_threads.restype = ctypes.c_int64
     return lib
 
 
@@ -59,3 +64,13 @@ def test_slab_loads_stay_in_the_matrix(plan, ld):
 def test_no_slab_beyond_the_contraction(plan):
     for left in (0, -1, -64, -1000):
         assert plan.slab_bytes(8, 8, left) == 0
+
+
+@pytest.mark.parametrize("rows,V", [(1, 1), (4096, 151936), (8192, 1 << 18), (8192, 1 << 22),
+                                    (1 << 16, 1 << 19), (1 << 16, 1 << 22)])
+def test_grad_launch_within_the_runtime_limit(plan, rows, V):
+    """HIP refuses a launch of 2^32 work items or more in a dimension; rows (up to a chunk of 2^16)
+    and V (up to 2^22) at the ends of what the LM-head calls accept."""
+    n = plan.grad_rows(rows, V)
+    assert 1 <= n <= rows
+    assert n * plan.grad_threads(V) < 1 << 32
