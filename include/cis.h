@@ -349,8 +349,8 @@ int cis_loss_bwd_ex(const void* logits, int dtype, int64_t T, int64_t V, int64_t
  * cis_workspace_bytes_ex plus, per chunk row, 8 bytes per 64 vocabulary columns and 20 bytes,
  * and the row's float32 logits (with_grad = 1), and with gradients the bf16 dL/dz of one dL/dW
  * group (about 2*V*min(T, group) bytes; group as for cis_lmhead_loss_bwd) and partial sums of
- * dL/dh (8 to 32 times 4*H bytes per chunk row). Returns 0 for T < 0, V
- * outside [1, 2^22], H outside [1, 2^16], chunk outside [1, 2^16], n_seq < 0 or with_grad
+ * dL/dh (V/512, at most 8 to 32, times 4*H bytes per chunk row; none for V < 1024). Returns 0 for
+ * T < 0, V outside [1, 2^22], H outside [1, 2^16], chunk outside [1, 2^16], n_seq < 0 or with_grad
  * outside 0..2. */
 size_t cis_lmhead_workspace_bytes(int64_t T, int64_t V, int64_t H, int64_t chunk, int64_t n_seq,
                                   int with_grad);

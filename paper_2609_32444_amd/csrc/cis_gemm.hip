@@ -715,16 +715,16 @@ hipError_t launch_gemm_epi(GemmArgs g, GemmQueuePool& queues, int num_cu, hipStr
 
 // The number of splits with the shortest estimate: rounds of one unit per CU, each its share of
 // the contraction and kUnitSlabs for its start and epilogue, and the reduction's traffic at
-// 5 TB/s; in slabs of 1.35 us (measured of a full chip). A split keeps kMinSplitSlabs at least.
+// 5 TB/s; in slabs of 1.35 us (measured of a full chip). A split keeps kMinSplitLen at least.
 // 4096 x 2048 x 151936: 2 splits (1 unit per CU); 1777 x 1600 x 50257: 5 (245 units; 8 splits
 // make 392, a second round half empty).
 int64_t gemm_splitk_count(int64_t M, int64_t N, int64_t K, int64_t max_splits, int num_cu) {
-  constexpr double kUnitSlabs = 6, kMinSplitSlabs = 8, kReduceSlabs = 4 / (5e12 * 1.35e-6);
+  constexpr double kUnitSlabs = 6, kReduceSlabs = 4 / (5e12 * 1.35e-6);
   const int64_t tiles = ((M + kGemmTile - 1) / kGemmTile) * ((N + kGemmTile - 1) / kGemmTile);
   const double slabs = (double)K / kGemmBK;
   int64_t best = 1;
   double best_t = INFINITY;
-  for (int64_t s = 1; s <= max_splits && (s == 1 || slabs / s >= kMinSplitSlabs); ++s) {
+  for (int64_t s = 1; s <= max_splits && (s == 1 || K >= s * kMinSplitLen); ++s) {
     const double rounds = (double)((tiles * s + num_cu - 1) / num_cu);
     const double t = rounds * (2 * ceil(slabs / (2 * s)) + kUnitSlabs) +
                      (s > 1 ? kReduceSlabs * (s + 1) * (double)M * (double)N : 0);

@@ -85,7 +85,7 @@ constexpr size_t ws_bytes(int64_t T) { return ws_layout(T, 0).total; }
 //   then per row and 64-column block the pair (max, exp-sum) (float2[rows, ntv]), the sampled
 //   logit (float[rows]) and the gradient parameters (GradParams[rows])
 //   G   bf16[grows, ldv]   dL/dz of the rows of a dL/dW group (backward)
-//   P   float[lm_splits, rows, H]  split-K partials of dL/dh (backward)
+//   P   float[lm_splits, rows, H]  split-K partials of dL/dh (backward, where it is split)
 // with rows = min(T, chunk), grows = min(T, lm_dw_rows(chunk)) and row strides rounded up by
 // lm_stride.
 constexpr int64_t kLmMaxH = int64_t(1) << 16;
@@ -97,11 +97,15 @@ constexpr int64_t kLmMaxLd = int64_t(1) << 22;
 // Row stride of n elements: whole 128-byte lines of bf16, so that a product's slab rows do not
 // straddle two, where that adds at most an eighth; else 16-byte chunks.
 inline int64_t lm_stride(int64_t n) { return n >= 512 ? (n + 63) / 64 * 64 : (n + 7) / 8 * 8; }
-// Splits of the contraction of dL/dh that the partial buffer holds: with few tiles, as many as
-// fill 256 compute units (the buffer is then at most 64 MiB).
-inline int64_t lm_splits(int64_t rows, int64_t H) {
+// Splits of the contraction (V) of dL/dh that the partial buffer holds: with few tiles, as many as
+// fill 256 compute units (the buffer is then at most 64 MiB), but no more than the products use
+// (gemm_splitk_count: a split keeps kMinSplitLen of the contraction).
+constexpr int64_t kMinSplitLen = 512;
+inline int64_t lm_splits(int64_t rows, int64_t V, int64_t H) {
   const int64_t tiles = ((rows + 255) / 256) * ((H + 255) / 256);
-  return tiles >= 32 ? 8 : (tiles <= 8 ? 32 : 256 / tiles);
+  const int64_t fill = tiles >= 32 ? 8 : (tiles <= 8 ? 32 : 256 / tiles);
+  const int64_t len = V / kMinSplitLen;
+  return len < 1 ? 1 : len < fill ? len : fill;
 }
 // dL/dW is one product per group of consecutive chunks, up to kLmDwRows rows: fewer products
 // that accumulate into dL/dW. A group holds whole chunks when chunk is a multiple of 8, otherwise
@@ -144,8 +148,8 @@ inline LmLayout lm_layout(int64_t T, int64_t V, int64_t H, int64_t chunk, int64_
   if (bwd) {
     end += align_up((size_t)grows * (size_t)M.ldv * 2, 256);
     M.part = end;
-    M.splits = rows > 0 ? lm_splits(rows, H) : 1;
-    end += align_up((size_t)M.splits * (size_t)rows * (size_t)H * 4, 256);
+    M.splits = rows > 0 ? lm_splits(rows, V, H) : 1;
+    if (M.splits > 1) end += align_up((size_t)M.splits * (size_t)rows * (size_t)H * 4, 256);
   }
   M.total = end;
   return M;

@@ -208,9 +208,9 @@ def test_lmhead_workspace_bytes():
     ntv = (V + 255) // 256 * 4
     assert fwd >= loss + 4096 * (8 * ntv + 4 + 16) and fwd % 256 == 0
     assert fwd < 4096 * V                       # far less than one float32 chunk of logits
-    # the backward adds the chunk's float32 logits, W^T, the chunk's bf16 gradient and the two
-    # transposed operands
-    assert bwd >= fwd + 4 * 4096 * V + 2 * V * H + 2 * 4096 * V + 2 * (V + H) * 4096
+    # the backward adds the chunk's float32 logits, the bf16 gradient of a dL/dW group (all 16384
+    # rows here) and the partial sums of dL/dh
+    assert bwd >= fwd + 4 * 4096 * V + 2 * T * V + 8 * 4096 * H * 4
     # a chunk larger than the batch only needs the batch's rows
     assert f(100, 1000, 64, 4096, 0, True) == f(100, 1000, 64, 100, 0, True)
     assert f(T, V, H, 4096, 10, True) >= bwd
@@ -221,8 +221,33 @@ def test_lmhead_workspace_bytes():
     # the backward that never stores the logits needs exactly one float32 chunk less
     rec = cis.lmhead_workspace_bytes(T, V, H, 4096, 0, True, recompute=True)
     assert 4 * 4096 * V <= bwd - rec <= 4 * 4096 * (V + 8) + 256
-    assert rec >= fwd + 2 * V * H + 2 * 4096 * V
+    assert rec >= fwd + 2 * T * V + 8 * 4096 * H * 4
     assert cis.load_library().cis_lmhead_workspace_bytes(T, V, H, 4096, 0, 3) == 0
+
+
+def _up(n):
+    return (n + 255) // 256 * 256
+
+
+@pytest.mark.parametrize("T,V,H,chunk,group,splits", [
+    (16384, 151936, 2048, 4096, 16384, 8),      # 128 tiles of dL/dh
+    (1777, 50257, 1600, 4096, 1777, 8),         # 49
+    (256, 151936, 2048, 4096, 256, 32),         # 8
+    (512, 151936, 2048, 4096, 512, 16),         # 16
+    (777, 50257, 1536, 259, 259, 21),           # 12; a chunk that is not a multiple of 8
+    (4096, 2048, 512, 1024, 4096, 4),           # no more splits than 512 of V each
+    (256, 1024, 2048, 4096, 256, 2), (256, 1023, 2048, 4096, 256, 1), (256, 8, 64, 64, 256, 1)])
+def test_lmhead_workspace_terms(T, V, H, chunk, group, splits):
+    """What the backward adds to the forward's workspace, term by term: the bf16 G of a dL/dW group
+    and, where dL/dh's contraction is split, its partial sums; without recompute also a chunk of
+    float32 logits. Rows of G and of the logits are whole 128-byte lines of bf16 from V = 512 on."""
+    f = cis.lmhead_workspace_bytes
+    rows, ld = min(T, chunk), (V + 63) // 64 * 64 if V >= 512 else (V + 7) // 8 * 8
+    fwd, rec, bwd = (f(T, V, H, chunk, 0, g, recompute=r)
+                     for g, r in ((False, False), (True, True), (True, False)))
+    partials = 4 * splits * rows * H if splits > 1 else 0
+    assert rec - fwd == _up(2 * group * ld) + _up(partials)
+    assert bwd - rec == _up(4 * rows * ld)
 
 
 # distinct fake buffers for the LM-head calls, 4 GiB apart (never dereferenced)
