@@ -389,6 +389,39 @@ int launch_seg_grad(const LossCall& c, const Ws& ws, const cis::SegGradVariant& 
   return CIS_OK;
 }
 
+// Byte range [lo, hi) of a rows x cols matrix with a row stride of ld elements of es bytes
+// (empty for a null pointer or no rows); hi saturates at the top of the address space.
+struct Span {
+  uintptr_t lo, hi;
+};
+
+Span span_of(const void* p, int64_t rows, int64_t cols, int64_t ld, int es) {
+  if (!p || rows <= 0 || cols <= 0) return Span{0, 0};
+  const unsigned __int128 n = ((unsigned __int128)(rows - 1) * (uint64_t)ld + (uint64_t)cols) *
+                              (unsigned)es;
+  const uintptr_t lo = (uintptr_t)p;
+  return Span{lo, n > (unsigned __int128)(UINTPTR_MAX - lo) ? UINTPTR_MAX : lo + (uintptr_t)n};
+}
+
+bool overlaps(Span a, Span b) { return a.lo < b.hi && b.lo < a.hi; }
+
+// Whether a per-row output lies over a per-row input. The row kernel allows that (a row's workgroup
+// alone reads its inputs, before it writes its outputs); in the pass over segments the row's other
+// workgroups may read them later.
+bool rows_alias(const LossCall& c) {
+  const int64_t T = c.T;
+  const Span ins[] = {span_of(c.ids, 1, T, T, 8), span_of(c.logp_infer, 1, T, T, 4),
+                      span_of(c.logp_old, 1, T, T, 4), span_of(c.adv, 1, T, T, 4),
+                      span_of(c.mask, 1, T, T, 1)};
+  const Span outs[] = {span_of(c.logp_train_out, 1, T, T, 4), span_of(c.w_out, 1, T, T, 4),
+                       span_of(c.terms_out, 1, T, T, 4), span_of(c.eps_out, 1, T, T, 4),
+                       span_of(c.acted_out, 1, T, T, 1)};
+  for (const Span& o : outs)
+    for (const Span& i : ins)
+      if (overlaps(o, i)) return true;
+  return false;
+}
+
 int run_loss(const LossCall& c, hipStream_t stream) {
   const bool bwd = c.bwd;
   const int64_t T = c.T, V = c.V;
@@ -412,7 +445,7 @@ int run_loss(const LossCall& c, hipStream_t stream) {
   const cis::WsLayout Lseg = cis::ws_layout(T, n_seq, true);
   const int32_t nvec = (int32_t)((V + 16 / esize - 1) / (16 / esize));
   const bool few = bwd && T > 0 && c.workspace_bytes >= Lseg.total &&
-                   cis::select_seg_grad_variant(c.dtype, c.ext, T, nvec, &sg);
+                   cis::select_seg_grad_variant(c.dtype, c.ext, T, nvec, &sg) && !rows_alias(c);
   if (few) L = Lseg;
   if (T > 0) {
     if (!aligned(c.logits, 16) || (c.ld * esize) % 16 != 0) return CIS_ERR_ALIGN;
@@ -466,22 +499,6 @@ int scratch_on(int dev, void** out) {
   *out = g_scratch[dev];
   return CIS_OK;
 }
-
-// Byte range [lo, hi) of a rows x cols matrix with a row stride of ld elements of es bytes
-// (empty for a null pointer or no rows); hi saturates at the top of the address space.
-struct Span {
-  uintptr_t lo, hi;
-};
-
-Span span_of(const void* p, int64_t rows, int64_t cols, int64_t ld, int es) {
-  if (!p || rows <= 0 || cols <= 0) return Span{0, 0};
-  const unsigned __int128 n = ((unsigned __int128)(rows - 1) * (uint64_t)ld + (uint64_t)cols) *
-                              (unsigned)es;
-  const uintptr_t lo = (uintptr_t)p;
-  return Span{lo, n > (unsigned __int128)(UINTPTR_MAX - lo) ? UINTPTR_MAX : lo + (uintptr_t)n};
-}
-
-bool overlaps(Span a, Span b) { return a.lo < b.hi && b.lo < a.hi; }
 
 // The loss on the logits hidden * W^T, a chunk of rows at a time (cis_lmhead_loss_fwd/_bwd).
 struct LmHeadCall {

@@ -180,6 +180,38 @@ def test_few_long_rows(V, T, dtype):
         assert torch.equal(o["terms"], out["terms"]) and torch.equal(o["loss"], out["loss"])
 
 
+# Per-row outputs that replace per-row inputs, at a size that otherwise takes segments: the call
+# keeps to the row kernel, whose rows belong to one workgroup each. Bit-equal to the row kernel's
+# results (a workspace without room for segments selects it).
+@pytest.mark.parametrize("out_key,in_key", [("logp_train", "logp_infer"), ("terms", "adv"),
+                                            ("w", "logp_infer"), ("trunc", "mask")])
+def test_outputs_over_inputs_few_long_rows(out_key, in_key):
+    T, V = 96, 151936
+    b = make_random_batch(T, V, torch.bfloat16, DEV, seed=23, mask_p=0.8)
+    store = {"logp_train": torch.empty(T, device=DEV), "w": torch.empty(T, device=DEV),
+             "terms": torch.empty(T, device=DEV), "loss": torch.empty(1, device=DEV),
+             "trunc": torch.empty(T, dtype=torch.uint8, device=DEV)}
+    ins = {"logp_infer": b.logp_infer.clone(), "adv": b.adv.clone(), "mask": b.mask.clone()}
+    ref = {k: torch.empty_like(v) for k, v in store.items()}
+    gref = torch.empty_like(b.logits)
+    lib, p = cis.load_library(), lambda t: t.data_ptr()
+    ws = torch.empty(18 * T + 4096, dtype=torch.uint8, device=DEV)   # the fused pass's own rows
+    rc = lib.cis_loss_bwd(p(b.logits), 0, T, V, b.logits.stride(0), p(b.ids), p(b.logp_infer),
+                          p(b.adv), p(b.mask), b.lam, b.kappa, b.scale, p(gref), gref.stride(0),
+                          p(ref["logp_train"]), p(ref["w"]), p(ref["trunc"]), p(ref["terms"]),
+                          p(ref["loss"]), p(ws), ws.numel(), 0)
+    assert rc == 0
+    store[out_key] = ins[in_key]
+    g = torch.empty_like(b.logits)
+    torch.cuda.synchronize()
+    cis.loss_bwd_noalloc(b.logits, b.ids, ins["logp_infer"], ins["adv"], ins["mask"], lam=b.lam,
+                         kappa=b.kappa, scale=b.scale, V=V, dlogits=g, outputs=store)
+    torch.cuda.synchronize()
+    for k in ref:
+        assert torch.equal(store[k], ref[k]), k
+    assert torch.equal(g.view(torch.int16), gref.view(torch.int16))
+
+
 # Forward pass: rows of fewer than 2048 16-byte vectors go through the row kernel (capacities
 # 128, 256, 512, 1024, 2048 vectors); rows of 2048 up to 131072 vectors through the split
 # kernels (segments of 1024, 2048 or 4096 vectors, at most 32 per row); longer rows through the
