@@ -317,8 +317,9 @@ int launch_rows(const LossCall& c, const Ws& ws, bool clear_queue, int dev,
     // one short-lived workgroup per (row, segment); the kernel loops only past 2^30 of them
     const int64_t total = rows * sa.nseg;
     const int64_t cap = int64_t(1) << 30;
-    if (hipLaunchKernel(sv->fn, dim3((unsigned)(total < cap ? total : cap)), dim3(sv->block),
-                        args, 0, stream) != hipSuccess)
+    if (hipLaunchKernel(sa.rot >= 0 ? sv->rotated : sv->fn,
+                        dim3((unsigned)(total < cap ? total : cap)), dim3(sv->block), args, 0,
+                        stream) != hipSuccess)
       return CIS_ERR_LAUNCH;
     return launch_combine(c, ra, sa, rows, stream);
   }

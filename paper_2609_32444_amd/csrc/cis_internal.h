@@ -209,24 +209,28 @@ struct SegArgs {
   int32_t segvec;   // 16-byte vectors per segment (split forward pass)
   int64_t stride;   // pieces per row in `part`
   GradParams* gp;   // [T] nullable: gradient parameters for the fused LM-head pass
-  uint32_t* done;   // nullable: rows whose outputs are stored (the fused pass over few rows)
+  uint32_t* done;   // rows whose outputs are stored (the fused pass over few rows)
   int32_t rot;      // seg_rotation() (split forward pass)
 };
 // Workgroup b runs on XCD b % 8, so the segment at a given place of the row meets the same XCD again
 // after 8 / gcd(nseg, 8) rows: one more place of rotation from then on. None (-1) for an odd nseg,
 // which visits every XCD by itself, and for equal segments: there the plain order is the faster one
-// (16384 rows of V = 151936 782 us against 798, V = 32768 171 against 178).
+// (16384 rows of V = 151936 782 us against 798, V = 32768 171 against 178). Nor for four segments
+// with the last one less than a quarter full (V = 24657 172.5 us against 175.8; from V = 26214 on the
+// two are within 1%, and float32 rows of V = 14336 gain: 85.7 and 79.8).
 inline int32_t seg_rotation(int32_t nseg, int32_t segvec, int32_t nvec) {
-  if (nseg % 2 != 0 || nvec % segvec == 0) return -1;
+  const int32_t last = nvec % segvec;
+  if (nseg % 2 != 0 || last == 0 || (nseg == 4 && 4 * last < segvec)) return -1;
   return nseg % 8 == 0 ? 0 : nseg % 4 == 0 ? 1 : 2;
 }
 constexpr int kCombineBlock = 256;
 constexpr int kSegGradBlock = 128, kSegGradK = 8;   // 16 KiB of logits per workgroup
 // A compiled segment kernel: `block` threads with K 16-byte vectors each, so block * K vectors
 // per segment.
+enum class SegUse { kPlain, kRotated, kGrad };
 struct SegVariant {
   int block, k;
-  const void* fn;
+  const void *fn, *rotated;   // segments in order, and rotated (seg_rotation)
 };
 // The segment kernel for rows of `nvec` vectors, or nullptr when the row kernel serves them
 // better (short rows) or they need more than kSegMax segments of the largest variant.

@@ -97,7 +97,9 @@ const RowVariant& select_row_variant(int dtype, bool bwd, int32_t nvec) {
 // row per workgroup is already a small independent read); longer rows take the first variant
 // that covers them with at most kSegMax segments.
 constexpr int32_t kSegMinVec = 2048;
-#define CIS_SEG(E, B, K, RE) SegVariant{B, K, (const void*)&cis_seg_kernel<E, B, K, RE>}
+#define CIS_SEG(E, B, K, RE)                                                 \
+  SegVariant{B, K, (const void*)&cis_seg_kernel<E, B, K, RE, SegUse::kPlain>, \
+             (const void*)&cis_seg_kernel<E, B, K, RE, SegUse::kRotated>}
 // 128-thread workgroups of 8 vectors each (16 KiB of bf16 logits) measured best at V = 32768,
 // 151936 and 262144 among 64-256 threads x 4-16 vectors; longer rows take longer segments.
 static const SegVariant kSegBf16[] = {CIS_SEG(Bf16, 128, 8, true), CIS_SEG(Bf16, 128, 16, true),
@@ -128,8 +130,8 @@ bool select_seg_grad_variant(int dtype, bool ext, int64_t T, int32_t nvec, SegGr
   const bool b = dtype == CIS_BF16;
   *v = SegGradVariant{
       kSegGradBlock, kSegGradK,
-      b ? (const void*)&cis_seg_kernel<Bf16, kSegGradBlock, kSegGradK, true, 0>
-        : (const void*)&cis_seg_kernel<F32, kSegGradBlock, kSegGradK, true, 0>,
+      b ? (const void*)&cis_seg_kernel<Bf16, kSegGradBlock, kSegGradK, true, SegUse::kGrad>
+        : (const void*)&cis_seg_kernel<F32, kSegGradBlock, kSegGradK, true, SegUse::kGrad>,
       ext ? seg_grad_kernel_ext(dtype)
       : b ? (const void*)&cis_seg_grad_kernel<Bf16, kSegGradBlock, kSegGradK, false>
           : (const void*)&cis_seg_grad_kernel<F32, kSegGradBlock, kSegGradK, false>};

@@ -32,21 +32,23 @@ namespace cis {
 
 // BLOCK threads take a segment of BLOCK * K vectors. RE: re-unpack the vectors for the
 // exp-sum instead of keeping K * EPV floats alive from the max pass (fewer registers, one more
-// VALU operation per logit).
-template <class E, int BLOCK, int K, bool RE, int AUX = kAuxNT>
+// VALU operation per logit). USE (compile-time: the test of a rotation at run time cost the plain
+// order 2%): the segments in order, rotated, or for cis_seg_grad_kernel.
+template <class E, int BLOCK, int K, bool RE, SegUse USE>
 __global__ __launch_bounds__(BLOCK) void cis_seg_kernel(const RowArgs a, const SegArgs g) {
   constexpr int EPV = E::kPerVec;
   constexpr int NW = BLOCK / 64;
+  constexpr int AUX = USE == SegUse::kGrad ? 0 : kAuxNT;
   __shared__ float sh_m[NW];
   __shared__ float sh_s[NW];
   const int V = a.V;
   const int64_t total = a.T * (int64_t)g.nseg;
-  if (g.done && blockIdx.x == 0 && threadIdx.x == 0) *g.done = 0u;
+  if (USE == SegUse::kGrad && blockIdx.x == 0 && threadIdx.x == 0) *g.done = 0u;
   for (int64_t b = blockIdx.x; b < total; b += gridDim.x) {
     int tid = threadIdx.x;
     const int64_t row = b / g.nseg;
     int seg = (int)(b - row * g.nseg);
-    if (AUX == kAuxNT && g.rot >= 0) {
+    if (USE == SegUse::kRotated) {
       seg += (int)((uint32_t)(row >> g.rot) % (uint32_t)g.nseg);
       if (seg >= g.nseg) seg -= g.nseg;
     }
