@@ -324,7 +324,8 @@ int launch_rows(const LossCall& c, const Ws& ws, bool clear_queue, int dev,
     return launch_combine(c, ra, sa, rows, stream);
   }
   int64_t resident = (int64_t)blocks_per_cu(var->fn, var->block, dev) * info.num_cu;
-  if (c.bwd && rows > info.num_cu && rows <= cis::few_rounds(nvec) * resident) {
+  if (c.bwd && rows > info.num_cu &&
+      rows <= cis::few_rounds(nvec, c.mask != nullptr) * resident) {
     const cis::RowVariant* few = c.ext ? cis::select_row_variant_few_ext(c.dtype, nvec)
                                        : cis::select_row_variant_few(c.dtype, nvec);
     if (few) {

@@ -339,9 +339,14 @@ const RowVariant& select_row_variant_ext(int dtype, bool bwd, int32_t nvec);
 const void* finalize_kernel(int block, bool parts);
 // The fused variant for calls of few rows per workgroup of the variant above that the chip holds at
 // once (at most few_rounds, and more than one row per CU), or null where there is none (see
-// CIS_FEW_TABLE).
-inline int64_t few_rounds(int32_t nvec) {
-  return nvec > 4096 ? 6 : nvec > 3584 ? 16 : nvec > 2048 ? 0 : 4;
+// CIS_FEW_TABLE). With a mask no more than 4: a workgroup's first three rows are fixed, and over
+// more rounds than that the smaller blocks, which are more, leave too few rows to the queue to make
+// up for masked ones (half of the rows masked: V = 32768, 3001 rows 65.9 us with the ladder's blocks
+// and 74.9 with these, 4096 rows 86.6 and 93.1; V = 50257, 1536 rows 62.1 and 64.4; V = 65536, 1300
+// rows 60.8 and 65.6; up to 4 rounds these are the faster ones or equal, masked or not).
+inline int64_t few_rounds(int32_t nvec, bool masked) {
+  if (nvec > 2048 && nvec <= 3584) return 0;
+  return masked || nvec <= 2048 ? 4 : nvec > 4096 ? 6 : 16;
 }
 const RowVariant* select_row_variant_few(int dtype, int32_t nvec);
 const RowVariant* select_row_variant_few_ext(int dtype, int32_t nvec);

@@ -1177,12 +1177,14 @@ __global__ __launch_bounds__(BLOCK) void cis_row_kernel(const RowArgs a) {
    CIS_V(E, 1024, 11, 0, true, false), CIS_V(E, 1024, 15, 0, true, false),                  \
    CIS_V(E, 1024, 18, 0, true, false), CIS_V(E, 1024, 18, 9, true, false)}
 // Fused calls of at most few_rounds() rows per resident workgroup of that ladder: smaller blocks, so
-// that more rows are in flight per compute unit and the last round costs less. bf16, ladder and
-// these, us per call: V = 16384, 3001 rows 48.5 and 41.4, 4096 rows (5.3 rounds) 61.2 and 63.0;
-// V = 32768, 1024 rows 36.8 and 26.3, 4096 rows (16 rounds) 116.3 and 114.9, 8192 rows 210 and 218;
-// V = 36000, 1024 rows 40.4 and 33.4; V = 50257, 1024 rows 51.5 and 44.4 (512 x 13), 3001 rows 127
-// and 127, 16384 rows 598 and 677. Between 2049 and 3584 vectors the ladder's own blocks are the
-// better ones at every count (V = 20000, 1024 rows 17.5 against 19.6).
+// that more rows are in flight per compute unit and the last round costs less. Without a mask, ladder
+// and these, us per call (bf16 unless float32 is said): V = 16384, 3001 rows 48.5 and 41.4, 4096 rows
+// (5.3 rounds) 61.2 and 63.0; V = 32768, 1024 rows 38.8 and 24.1, 4096 rows 117.5 and 112.8, 8192 rows
+// (16 rounds) 213.5 and 212.8; V = 28680 in the same way 37.6 and 21.3, 112.0 and 102.2, 205.6 and
+// 208.3; float32 V = 14400 36.8 and 20.4, 104.1 and 92.2, 189.9 and 189.2; V = 36000, 1024 rows 40.4
+// and 33.4; V = 50257, 1024 rows 51.5 and 44.4 (512 x 13), 3001 rows 127 and 127, 16384 rows 598 and
+// 677. Between 2049 and 3584 vectors the ladder's own blocks are the better ones at every count
+// (V = 20000, 1024 rows 17.5 against 19.6).
 #define CIS_FEW_TABLE(E)                                                                    \
   {CIS_V(E, 256, 7, 0, true, false), CIS_V(E, 256, 15, 0, true, false),                     \
    CIS_V(E, 512, 15, 0, true, false)}

@@ -3,6 +3,7 @@ row-kernel variant (register-resident and streamed rows), row strides, empty and
 batches, invalid ids, extreme probabilities, kappa = 0, lambda = 0, in-place gradients, float32
 logits, the elementwise weight kernel, and argument errors raised through the binding."""
 
+import dataclasses
 import math
 
 import numpy as np
@@ -124,6 +125,15 @@ def test_blocks_by_row_count(V, T, dtype):
     b = make_random_batch(T, V, dtype, DEV, seed=V % 83, ld=((V + epv - 1) // epv) * epv,
                           mask_p=0.5)
     run_and_check(b)
+
+
+@pytest.mark.parametrize("V,T,dtype", [
+    (28673, 3001, torch.bfloat16), (32768, 3080, torch.bfloat16), (50257, 1536, torch.bfloat16),
+    (50257, 1537, torch.bfloat16), (14337, 3080, torch.float32)])
+def test_blocks_by_row_count_without_a_mask(V, T, dtype):
+    epv = 8 if dtype == torch.bfloat16 else 4
+    b = make_random_batch(T, V, dtype, DEV, seed=V % 73, ld=((V + epv - 1) // epv) * epv)
+    run_and_check(dataclasses.replace(b, mask=None))
 
 
 # The row kernel's long-row variants, at and just past their capacities, with more rows than the
