@@ -72,13 +72,13 @@ def test_long_rows_many_per_workgroup(V, dtype):
     run_and_check(b)
 
 
-# Fused-pass rows come from a queue once every workgroup has had two rows. The row counts put
-# thousands of rows in the queue for the one-wave, 512-thread, 1024-thread and LDS variants
-# (resident grids of up to 7168, 768, 256 and 256 workgroups). The queue is eight counters, each
-# handing out every eighth row; 515 and 517 rows of 151936 leave 3 and 5 queued rows on a grid
-# of 256, so most counters are empty from the start and the workgroups on them must move on.
-@pytest.mark.parametrize("V,T", [(1000, 20000), (32768, 4096), (151936, 1500), (250001, 700),
-                                 (151936, 515), (151936, 517)])
+# Fused-pass rows of more than one wave come from a queue once every workgroup has had three rows.
+# The row counts put hundreds to thousands of rows in the queue for the 512-thread and 1024-thread
+# variants with eight counters (each hands out every eighth row), the 1024-thread one with one
+# counter and the LDS variant; 771 and 773 rows of 151936 leave 3 and 5 queued rows on a grid of 256.
+# (1000, 20000) is one-wave rows, which take fixed ones.
+@pytest.mark.parametrize("V,T", [(1000, 20000), (20000, 4000), (32768, 4096), (151936, 1500),
+                                 (250001, 900), (151936, 771), (151936, 773)])
 def test_row_queue_and_stale_workspace(V, T):
     """The workspace starts as all 0xFF bytes: as the row queue's counter that would hand out
     no queued row at all, so the call must clear it itself. Every row (15% masked) against the
@@ -96,18 +96,22 @@ def test_row_queue_and_stale_workspace(V, T):
     assert torch.equal(out2["terms"], t1)
 
 
-# Calls that take no row from a queue (up to three per workgroup) and the first that does, with
-# eight and with one counter; and row counts about the steps of the statistics reduction (one
-# workgroup of 256 threads up to 1024 rows, one of 1024 up to 16384, then parts of 4096 rows).
-@pytest.mark.parametrize("V,T", [(151936, 768), (151936, 769), (32768, 1536), (32768, 1545),
-                                 (40, 1024), (40, 1025), (40, 16384), (40, 16385), (40, 40963)])
+# Calls that take no row from a queue (up to three per workgroup) and the first that do: with one
+# counter (a grid of 256), and with eight, most of which are empty from the start, so that the
+# workgroups on them must move on to the next (a grid of 256, 512, 768 or 1024 workgroups, whichever
+# the device holds of the variant for V = 20000). And row counts about the steps of the statistics
+# reduction (one workgroup of 256 threads up to 1024 rows, one of 1024 up to 16384, then parts of
+# 4096 rows).
+@pytest.mark.parametrize("V,T", [(151936, 768), (151936, 769)] +
+                                [(20000, 768 * k + d) for k in (1, 2, 3, 4) for d in (1, 9)] +
+                                [(40, 1024), (40, 1025), (40, 16384), (40, 16385), (40, 40963)])
 def test_fixed_rows_and_statistics_parts(V, T):
     test_row_queue_and_stale_workspace(V, T)
 
 
-# Calls of a few rows per workgroup take smaller blocks (CIS_FEW_TABLE; test_bf16_vocab_sizes and
-# test_f32_vocab_sizes are such calls): the ladder's own variants with more rows than that, at and
-# just past their capacities, and the smaller blocks at theirs.
+# Calls of a few rows per workgroup take smaller blocks (CIS_FEW_TABLE): the ladder's own variants
+# with more rows than that, at and just past their capacities, and the smaller blocks at theirs.
+# Without a mask they take them up to more rows: on either side of that limit.
 @pytest.mark.parametrize("V,T,dtype", [
     (8193, 4000, torch.bfloat16), (16384, 4000, torch.bfloat16), (16385, 2200, torch.bfloat16),
     (32768, 2200, torch.bfloat16), (32769, 2200, torch.bfloat16), (65530, 1300, torch.bfloat16),
@@ -281,12 +285,14 @@ def test_all_masked_and_invalid_ids(V, bwd):
         assert torch.count_nonzero(out["dlogits"][bad]) == 0
 
 
-@pytest.mark.parametrize("V,bwd", [(5000, True), (5000, False), (151936, True), (151936, False)])
-def test_confident_rows_and_extremes(V, bwd):
+@pytest.mark.parametrize("V,T,bwd", [(5000, 16, True), (5000, 16, False), (151936, 16, True),
+                                     (151936, 16, False), (32768, 16, True), (151936, 200, True),
+                                     (250001, 200, True)])
+def test_confident_rows_and_extremes(V, T, bwd):
     """p -> 1 (1 - p down to ~1e-30), l_infer = -inf, z_y = -inf, -inf and huge-negative logits;
-    fused and forward only, on short rows and on rows of the split forward pass."""
-    T = 16
-    b = make_random_batch(T, V, torch.bfloat16, DEV, seed=4, mask_p=1.0)
+    fused and forward only: one-wave rows, rows of the split forward pass and of the fused pass
+    over segments (16 rows of 151936), rows of several waves, and rows with LDS and streamed slots."""
+    b = make_random_batch(T, V, torch.bfloat16, DEV, seed=4, mask_p=1.0, ld=(V + 7) // 8 * 8)
     z = b.logits
     y = b.ids
     for t, gap in enumerate([5, 10, 15, 20, 30, 40, 60, 80]):
@@ -321,13 +327,14 @@ def test_threshold_and_floor_settings(kappa, c):
         assert np.allclose(w, np.minimum(k, 1.0), rtol=1e-5)
 
 
-@pytest.mark.parametrize("V,ld", [(9001, 9008), (151936, 151936), (200003, 200016)])
-def test_in_place_gradient(V, ld):
+@pytest.mark.parametrize("V,ld,T", [(9001, 9008, 40), (151936, 151936, 40), (200003, 200016, 40),
+                                    (151936, 151936, 200), (200003, 200016, 200)])
+def test_in_place_gradient(V, ld, T):
     # The gradient overwrites the logits row by row (each element is read before the same
     # thread writes it). Checked against the oracle on the original logits, and bit for bit
     # against a separate output buffer.
-    b = make_random_batch(40, V, torch.bfloat16, DEV, seed=9, ld=ld)
-    store = torch.empty(2, 40, ld, dtype=torch.bfloat16, device=DEV)
+    b = make_random_batch(T, V, torch.bfloat16, DEV, seed=9, ld=ld)
+    store = torch.empty(2, T, ld, dtype=torch.bfloat16, device=DEV)
     store[0, :, :V] = b.logits
     buf = store[0, :, :V]
     sep = store[1, :, :V]

@@ -77,10 +77,12 @@ def _replay_and_compare(g, out, inputs, datasets, eager, keys):
 
 # (700 rows of 5003: every row is a workgroup's first or second; 3000 rows of 151936 on the
 # 256-workgroup grid: 2488 rows come from the row queue, whose counter the captured call
-# clears with a kernel node on every replay)
+# clears with a kernel node on every replay; 96 rows of 151936: the pass over segments, whose
+# statistics wait for a counter that the call's first kernel clears)
 @pytest.mark.parametrize("dtype,T,V,ld", [(torch.bfloat16, 700, 5003, 5008),
                                           (torch.float32, 700, 5003, 5008),
-                                          (torch.bfloat16, 3000, 151936, 151936)])
+                                          (torch.bfloat16, 3000, 151936, 151936),
+                                          (torch.bfloat16, 96, 151936, 151936)])
 def test_fused_loss_graph_replays(dtype, T, V, ld):
     b = make_random_batch(T, V, dtype=dtype, device=DEV, seed=21, mask_p=0.9, ld=ld)
     b2 = make_random_batch(T, V, dtype=dtype, device=DEV, seed=22, mask_p=0.9, ld=ld)
@@ -97,8 +99,10 @@ def test_fused_loss_graph_replays(dtype, T, V, ld):
                         eager, ("logp_train", "w", "trunc", "terms", "loss", "dlogits"))
 
 
-def test_decoupled_loss_graph_replays():
-    T, V, ld = 600, 7001, 7008
+@pytest.mark.parametrize("T,V,ld", [(600, 7001, 7008), (4000, 20001, 20008),
+                                    (96, 151936, 151936)])
+def test_decoupled_loss_graph_replays(T, V, ld):
+    """One-wave rows; rows from the queue, which the pre-pass clears; the pass over segments."""
     b = make_random_batch(T, V, device=DEV, seed=31, mask_p=0.95, ld=ld)
     b2 = make_random_batch(T, V, device=DEV, seed=32, mask_p=0.95, ld=ld)
     gen = torch.Generator(device=DEV)

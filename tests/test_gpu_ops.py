@@ -127,16 +127,20 @@ def test_forward_only_ex_matches_fused():
         assert torch.all(d <= 1e-5 * f[k].double().abs() + 2e-6), k
 
 
-@pytest.mark.parametrize("V,dtype,op,kw", [
-    (200003, torch.bfloat16, X.OP_TIS, dict(hi=2.0)),          # LDS-resident slots
-    (262144, torch.bfloat16, X.OP_ICEPOP, dict(lo=0.5, hi=5.0)),  # streamed remainder
-    (90001, torch.float32, X.OP_CIS, dict(lam=2.3, kappa=5e-3)),
-    (4097, torch.float32, X.OP_KPOP, dict(hi=0.05)),
+# 24 long rows go through the pass over segments, 200 through the row kernel.
+@pytest.mark.parametrize("V,T,dtype,op,kw", [
+    (200003, 24, torch.bfloat16, X.OP_TIS, dict(hi=2.0)),
+    (262144, 24, torch.bfloat16, X.OP_ICEPOP, dict(lo=0.5, hi=5.0)),
+    (90001, 24, torch.float32, X.OP_CIS, dict(lam=2.3, kappa=5e-3)),
+    (200003, 200, torch.bfloat16, X.OP_TIS, dict(hi=2.0)),          # LDS-resident slots
+    (262144, 200, torch.bfloat16, X.OP_ICEPOP, dict(lo=0.5, hi=5.0)),  # streamed remainder
+    (90001, 200, torch.float32, X.OP_CIS, dict(lam=2.3, kappa=5e-3)),
+    (4097, 24, torch.float32, X.OP_KPOP, dict(hi=0.05)),
 ])
-def test_decoupled_long_and_float32_rows(V, dtype, op, kw):
-    b = small_batch(V=V, T=24, dtype=dtype, seed=V % 1000)
+def test_decoupled_long_and_float32_rows(V, T, dtype, op, kw):
+    b = small_batch(V=V, T=T, dtype=dtype, seed=V % 1000)
     lold = old_logprobs(b, sd=0.3, seed=2)
-    run_case(f"decoupled_V{V}_{str(dtype)[6:]}", b, op, kw, logp_old=lold)
+    run_case(f"decoupled_V{V}_T{T}_{str(dtype)[6:]}", b, op, kw, logp_old=lold)
 
 
 def test_decoupled_many_rows_per_workgroup():

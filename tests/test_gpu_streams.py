@@ -36,9 +36,11 @@ def _concurrent(calls):
     return outs
 
 
-def test_fused_loss_on_two_streams():
-    batches = [make_random_batch(2048, 32000, device=DEV, seed=s, mask_p=0.9, ld=32000)
-               for s in (41, 42)]
+@pytest.mark.parametrize("T,V", [(2048, 32000), (4096, 32000), (96, 151936)])
+def test_fused_loss_on_two_streams(T, V):
+    """Fixed rows only; rows from the queue; the pass over segments, with its counter of finished
+    rows."""
+    batches = [make_random_batch(T, V, device=DEV, seed=s, mask_p=0.9, ld=V) for s in (41, 42)]
     calls = [cis.LossCall(b.logits, b.ids, b.logp_infer, b.adv, b.mask, lam=b.lam,
                           kappa=b.kappa, scale=b.scale) for b in batches]
     seq = []
