@@ -50,7 +50,8 @@ def kernel_source_hash(extra=()) -> str:
     for f in ("paper_2609_32444_amd/csrc/cis_row.h", "paper_2609_32444_amd/csrc/cis_kernels.hip",
               "paper_2609_32444_amd/csrc/cis_kernels_ext.hip",
               "paper_2609_32444_amd/csrc/cis_api.cpp", "paper_2609_32444_amd/csrc/cis_internal.h",
-              "paper_2609_32444_amd/csrc/cis_seg.h", "paper_2609_32444_amd/csrc/cis_stats.h", *extra):
+              "paper_2609_32444_amd/csrc/cis_seg.h", "paper_2609_32444_amd/csrc/cis_stats.h",
+              "paper_2609_32444_amd/csrc/cis_plan.h", *extra):
         with open(os.path.join(ROOT, f), "rb") as fh:
             h.update(fh.read())
     return h.hexdigest()[:16]
@@ -101,8 +102,7 @@ def lmhead_traffic():
         return None
 
 
-LMHEAD_SOURCES = ("paper_2609_32444_amd/csrc/cis_gemm.hip", "paper_2609_32444_amd/csrc/cis_gemm.h",
-                  "paper_2609_32444_amd/csrc/cis_plan.h")
+LMHEAD_SOURCES = ("paper_2609_32444_amd/csrc/cis_gemm.hip", "paper_2609_32444_amd/csrc/cis_gemm.h")
 
 
 PROBE_MAX_ROW_BYTES = 19 * 1024 * 16   # the row-pattern probes hold one row per workgroup

@@ -133,26 +133,18 @@ int launch_grid_stride(const void* fn, int64_t T, int block, const DeviceInfo& i
   return launch(fn, grid_stride_blocks(T, block, info), block, arg, stream);
 }
 
-// Sequence operators: per-response log K for the pre-pass `pa`, and the kernel that sums it. A
-// wave per response up to kSeqWaveLen tokens on average (a workgroup of 1024 threads would idle
-// there), else workgroups: with few long responses several for each, as far as their sums fit
-// the head of the workspace and have 2048 tokens each (two per thread).
-constexpr int64_t kSeqWaveLen = 512;
+// Sequence operators: per-response log K for the pre-pass `pa`, and the kernel that sums it, by the
+// waves or workgroups of seq_pieces; several sums of a response lie at the head of the workspace.
 int launch_seq_sum(const float* lp, const float* lq, const uint8_t* mask, const int64_t* ids,
                    int64_t V, const int64_t* offsets, int64_t n_seq, int64_t T, const Ws& ws,
                    cis::PrepassArgs* pa, hipStream_t stream) {
-  const int64_t avg = T / n_seq;
-  int64_t pieces = 1;
-  if (avg > kSeqWaveLen) {
-    const int64_t fit = cis::kSeqPieceSums / n_seq, work = avg / 2048;
-    pieces = fit < work ? fit : work;
-    if (pieces < 1) pieces = 1;
-  }
+  const int64_t blocks = cis::seq_pieces(T, n_seq, cis::kSeqPieceSums);
+  const int32_t pieces = blocks > 1 ? (int32_t)blocks : 1;
   double* logK = reinterpret_cast<double*>(ws.base + (pieces > 1 ? cis::kQueueOff : ws.L.logK));
-  cis::SeqSumArgs sa{lp, lq, mask, ids, offsets, logK, T, n_seq, (int32_t)V, (int32_t)pieces};
+  cis::SeqSumArgs sa{lp, lq, mask, ids, offsets, logK, T, n_seq, (int32_t)V, pieces};
   pa->logK = logK;
-  pa->pieces = (int32_t)pieces;
-  if (avg <= kSeqWaveLen)
+  pa->pieces = pieces;
+  if (blocks == 0)
     return launch(cis::seq_sum_kernel(64), (int)((n_seq + 3) / 4), 256, &sa, stream);
   return launch(cis::seq_sum_kernel(cis::kSeqBlock), (int)(n_seq * pieces), cis::kSeqBlock, &sa,
                 stream);

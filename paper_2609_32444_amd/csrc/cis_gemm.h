@@ -5,7 +5,6 @@
 #include <stdint.h>
 
 #include "cis_internal.h"
-#include "cis_plan.h"
 
 namespace cis {
 

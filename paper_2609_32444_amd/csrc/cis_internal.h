@@ -6,6 +6,7 @@
 #include <stdint.h>
 
 #include "../../include/cis.h"
+#include "cis_plan.h"
 
 namespace cis {
 
@@ -358,6 +359,5 @@ const void* seq_sum_kernel(int threads);  // 64 (a wave per response) or kSeqBlo
 const void* prepass_kernel();
 constexpr int kFinalizeBlock = 1024;
 constexpr int kWeightsBlock = 256;
-constexpr int kSeqBlock = 1024;     // threads of a piece of a long response
 
 }  // namespace cis

@@ -34,4 +34,20 @@ constexpr int64_t grad_rows(int64_t rows, int64_t V) {
   return rows < most ? rows : most;
 }
 
+// Workgroups of kSeqBlock threads that sum a response's log K, or 0: a wave for each response. A
+// wave up to kSeqWaveLen tokens on average (a workgroup would idle there), and with more responses
+// than the work items of a launch allow workgroups of (HIP refuses 2^32; a wave each takes 64). With
+// few long responses several workgroups for each, as far as their sums fit (`sums` of them in all) and
+// have 2048 tokens each (two per thread).
+constexpr int kSeqBlock = 1024;
+constexpr int64_t kSeqWaveLen = 512;
+constexpr int64_t kSeqMaxBlocks = int64_t(1) << 20;
+constexpr int64_t seq_pieces(int64_t T, int64_t n_seq, int64_t sums) {
+  const int64_t avg = T / n_seq;
+  if (avg <= kSeqWaveLen || n_seq > kSeqMaxBlocks) return 0;
+  const int64_t fit = sums / n_seq, work = avg / 2048;
+  const int64_t pieces = fit < work ? fit : work;
+  return pieces < 1 ? 1 : pieces;
+}
+
 }  // namespace cis

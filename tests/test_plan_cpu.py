@@ -17,6 +17,8 @@ SOURCE = """
 extern "C" {
 uint32_t slab_bytes(uint32_t cols, uint32_t ld, int left) { return cis::slab_bytes(cols, ld, left); }
 int64_t grad_rows(int64_t rows, int64_t V) { return cis::grad_rows(rows, V); }
+int64_t seq_pieces(int64_t T, int64_t n_seq) { return cis::seq_pieces(T, n_seq, 128); }
+int64_t seq_block() { return cis::kSeqBlock; }
 int64_t grad_threads(int64_t V) { return cis::grad_tiles(V) * cis::kGradThreads; }
 }
 """
@@ -34,6 +36,8 @@ def plan(tmp_path_factory):
     lib.slab_bytes.restype = ctypes.c_uint32
     lib.grad_rows.argtypes = [ctypes.c_int64, ctypes.c_int64]
     lib.grad_threads.argtypes = [ctypes.c_int64]
+    lib.seq_pieces.argtypes = [ctypes.c_int64, ctypes.c_int64]
+    lib.seq_pieces.restype = lib.seq_block.restype = ctypes.c_int64
     lib.grad_rows.restype = lib.grad_threads.restype = ctypes.c_int64
     return lib
 
@@ -74,3 +78,15 @@ def test_grad_launch_within_the_runtime_limit(plan, rows, V):
     n = plan.grad_rows(rows, V)
     assert 1 <= n <= rows
     assert n * plan.grad_threads(V) < 1 << 32
+
+
+@pytest.mark.parametrize("T", [1, 513, 1 << 20, 1 << 31, 1 << 33, 1 << 36])
+def test_response_sums_within_the_runtime_limit(plan, T):
+    """The launch that sums the responses' log K stays below 2^32 work items for any number of
+    responses that a wave each allows (2^26 - 4), however long they are; several workgroups per
+    response only where their sums fit."""
+    most = (1 << 26) - 4
+    for n in (1, 2, 7, 128, 129, min(T // 513 + 1, most), 1 << 20, (1 << 20) + 1, 1 << 22, most):
+        p = plan.seq_pieces(T, n)
+        assert (n * p * plan.seq_block() if p else (n + 3) // 4 * 256) < 1 << 32, n
+        assert p <= 1 or n * p <= 128
