@@ -592,24 +592,24 @@ int run_lmhead(const LmHeadCall& m, hipStream_t stream) {
         return rc;
     }
     // dL/dh_c = G W
-    if (int rc = ok(cis::launch_gemm(
+    if (int rc = ok(cis::launch_gemm_nn(
             cis::gemm_args(Gc, m.weight, m.dhidden + t0 * m.ld_dh, tc, H, V, LM.ldv, m.ld_w,
                            m.ld_dh),
-            false, false, part, LM.splits, queues, ncu, stream)))
+            part, LM.splits, queues, ncu, stream)))
       return rc;
     // dL/dW (+)= G^T h over the group's rows, once its last chunk is in
     const int64_t gend = g0 + group < T ? g0 + group : T;
     if (t0 + tc < gend) continue;
-    if (int rc = ok(cis::launch_gemm(
+    if (int rc = ok(cis::launch_gemm_tn(
             cis::gemm_args(G, hid + g0 * m.ld_h, m.dweight, V, H, gend - g0, LM.ldv, m.ld_h,
                            m.ld_dw),
-            true, m.accumulate || g0 > 0, nullptr, 1, queues, ncu, stream)))
+            m.accumulate || g0 > 0, queues, ncu, stream)))
       return rc;
   }
   if (bwd && T == 0 && !m.accumulate) {  // no rows: dL/dW = 0 (an empty contraction)
-    if (int rc = ok(cis::launch_gemm(
-            cis::gemm_args(m.weight, m.weight, m.dweight, V, H, 0, 8, 8, m.ld_dw), true, false,
-            nullptr, 1, queues, ncu, stream)))
+    if (int rc = ok(cis::launch_gemm_tn(
+            cis::gemm_args(m.weight, m.weight, m.dweight, V, H, 0, 8, 8, m.ld_dw), false, queues,
+            ncu, stream)))
       return rc;
   }
   return launch_finalize(ws, T, c.loss_out, stream);

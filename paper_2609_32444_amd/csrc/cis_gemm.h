@@ -27,25 +27,24 @@ struct GemmEpi {
   int64_t ldg;
 };
 
-// C[M, N] (float32, row stride ldc) = alpha * A * B (+ C when accumulating), or one of the row-loss
+// C[M, N] (float32, row stride ldc) = A * B (+ C when accumulating), or one of the row-loss
 // epilogues above instead of C. A and B are bf16. For the epilogues A is [M, K] and B is [N, K],
-// both row-major; for launch_gemm B is [K, N] and A is [M, K], or [K, M] with a_kmajor. Row strides
-// lda, ldb are multiples of 8 elements, at most 2^22, and bases 16-byte aligned; a matrix's rows
-// are mapped up to a multiple of 8 elements. Any M, N, K >= 0. The fields after alpha are set by
-// the launches.
+// both row-major; launch_gemm_nn takes A as [M, K] and B as [K, N], launch_gemm_tn A as [K, M] and
+// B as [K, N]. Row strides lda, ldb are multiples of 8 elements, at most 2^22, and bases 16-byte
+// aligned; a matrix's rows are mapped up to a multiple of 8 elements. Any M, N, K >= 0. The fields
+// after ldc are set by the launches.
 struct GemmArgs {
   const void* A;
   const void* B;
   float* C;
   int64_t M, N, K, lda, ldb, ldc;
-  float alpha;
   bool m_fastest;           // tile order: M tiles fastest
   bool c_vec;               // C rows and base allow 16-byte stores
   int64_t k_split;          // contraction length per split
   int64_t c_split_stride;   // elements between the splits' partial outputs
   int64_t units;            // tiles x splits
   int* queue;               // kGemmQueues work counters (zero at launch), or null
-  int epi;                  // kEpiStore, kEpiLse or kEpiGrad
+  int epi;                  // kEpiStore, or a row-loss epilogue (set by the caller)
   GemmEpi e;
 };
 
@@ -61,7 +60,6 @@ inline GemmArgs gemm_args(const void* A, const void* B, float* C, int64_t M, int
   g.lda = lda;
   g.ldb = ldb;
   g.ldc = ldc;
-  g.alpha = 1.f;
   return g;
 }
 
@@ -88,16 +86,21 @@ struct GemmQueuePool {
   hipError_t take(int** queue, hipStream_t stream);
 };
 
-// Number of K splits, up to max_splits, that launch_gemm uses for an M x N x K product.
+// Number of K splits, up to max_splits, that launch_gemm_nn uses for an M x N x K product.
 int64_t gemm_splitk_count(int64_t M, int64_t N, int64_t K, int64_t max_splits, int num_cu);
 
-// Launch on `stream`; `beta` adds the product to C instead of overwriting it. With `partial`
-// (float32, max_splits * M * N elements, 16-byte aligned) small products are split along K and
-// the partials summed in a fixed order. With more tiles than CUs, one workgroup per CU takes tiles from per-XCD queues until all are taken, so XCDs that run faster
-// take over tiles of slower ones. Results do not depend on it: a tile is computed the same way
-// by whichever workgroup takes it.
-hipError_t launch_gemm(GemmArgs g, bool a_kmajor, bool beta, float* partial, int64_t max_splits,
-                       GemmQueuePool& queues, int num_cu, hipStream_t stream);
+// Launches on `stream`. With more tiles than CUs, one workgroup per CU takes tiles from per-XCD
+// queues until all are taken, so XCDs that run faster take over tiles of slower ones. Results do
+// not depend on it: a tile is computed the same way by whichever workgroup takes it.
+//
+// A [M, K] * B [K, N] into C. Small products are split along K, up to max_splits, and the partials
+// (`partial`: float32, max_splits * M * N elements, 16-byte aligned; unused with max_splits = 1)
+// summed in a fixed order.
+hipError_t launch_gemm_nn(GemmArgs g, float* partial, int64_t max_splits, GemmQueuePool& queues,
+                          int num_cu, hipStream_t stream);
+// A^T * B, A [K, M] and B [K, N]; `beta` adds the product to C instead of overwriting it.
+hipError_t launch_gemm_tn(GemmArgs g, bool beta, GemmQueuePool& queues, int num_cu,
+                          hipStream_t stream);
 // The logits product of a row chunk with a row-loss epilogue (kEpiLse, kEpiGrad or
 // kEpiLseStore; no split-K; C only with kEpiLseStore): M rows of h, N = V columns of W.
 hipError_t launch_gemm_epi(GemmArgs g, GemmQueuePool& queues, int num_cu, hipStream_t stream);

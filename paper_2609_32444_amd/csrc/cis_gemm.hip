@@ -157,7 +157,7 @@ __device__ __forceinline__ void store_tile(const GemmArgs& g, const f32x4 (&acc)
 #pragma unroll
     for (int j = 0; j < kTn; ++j) {
       const int64_t n = n0 + wn * kGemmWaveN + j * 16 + 4 * fq;
-      f32x4 v = acc[i][j] * g.alpha;
+      f32x4 v = acc[i][j];
       if (vec && n + 3 < g.N) {
         if (BETA) v += *(const f32x4*)(crow + n);
         *(f32x4*)(crow + n) = v;
@@ -608,14 +608,12 @@ __global__ __launch_bounds__(kThreads) void gemm_bf16_kernel(const GemmArgs g) {
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
 }
 
-// C = alpha * sum_s P[s] (+ C): the split-K partials summed in split order.
+// C = sum_s P[s]: the split-K partials summed in split order.
 struct ReduceArgs {
   const float* P;
   float* C;
   int64_t M, N, ldc, split_stride;
   int32_t splits;
-  float alpha;
-  bool beta;
 };
 
 // Four elements per thread (VEC: rows of 16-byte vectors), the splits' loads independent.
@@ -633,8 +631,7 @@ __global__ __launch_bounds__(256) void splitk_reduce_kernel(const ReduceArgs r) 
 #pragma unroll 4
     for (int k = 0; k < r.splits; ++k)
       s += *(const vec*)(r.P + k * r.split_stride + m * r.N + n);
-    vec* c = (vec*)(r.C + m * r.ldc + n);
-    *c = r.beta ? s * r.alpha + *c : s * r.alpha;
+    *(vec*)(r.C + m * r.ldc + n) = s;
   }
 }
 
@@ -733,18 +730,27 @@ int64_t gemm_splitk_count(int64_t M, int64_t N, int64_t K, int64_t max_splits, i
   return best;
 }
 
-hipError_t launch_gemm(GemmArgs g, bool a_kmajor, bool beta, float* partial, int64_t max_splits,
-                       GemmQueuePool& queues, int num_cu, hipStream_t stream) {
+hipError_t launch_gemm_tn(GemmArgs g, bool beta, GemmQueuePool& queues, int num_cu,
+                          hipStream_t stream) {
   if (g.M <= 0 || g.N <= 0) return hipSuccess;
+  g.m_fastest = g.M <= g.N;
+  g.k_split = g.K > 0 ? g.K : 1;
+  g.c_split_stride = 0;
+  g.c_vec = ((uintptr_t)g.C % 16 == 0) && g.ldc % 4 == 0;
+  g.units = gemm_tiles(g);
+  const void* fn = beta ? (const void*)&gemm_bf16_kernel<true, kEpiStore, true, true>
+                        : (const void*)&gemm_bf16_kernel<false, kEpiStore, true, true>;
+  return launch_units(g, fn, queues, num_cu, stream);
+}
+
+hipError_t launch_gemm_nn(GemmArgs g, float* partial, int64_t max_splits, GemmQueuePool& queues,
+                          int num_cu, hipStream_t stream) {
+  if (g.M <= 0 || g.N <= 0) return hipSuccess;
+  const void* fn = (const void*)&gemm_bf16_kernel<false, kEpiStore, false, true>;
   // the smaller dimension's tiles run fastest
   g.m_fastest = g.M <= g.N;
-  const int64_t splits = partial ? gemm_splitk_count(g.M, g.N, g.K, max_splits, num_cu) : 1;
+  const int64_t splits = gemm_splitk_count(g.M, g.N, g.K, max_splits, num_cu);
   g.units = gemm_tiles(g) * splits;
-  if (beta && splits <= 1 && !a_kmajor) return hipErrorInvalidValue;   // no such product here
-  const void* fn = !a_kmajor ? (const void*)&gemm_bf16_kernel<false, kEpiStore, false, true>
-                   : beta && splits <= 1
-                       ? (const void*)&gemm_bf16_kernel<true, kEpiStore, true, true>
-                       : (const void*)&gemm_bf16_kernel<false, kEpiStore, true, true>;
   const bool c_aligned = ((uintptr_t)g.C % 16 == 0) && g.ldc % 4 == 0;
   if (splits <= 1) {
     g.k_split = g.K > 0 ? g.K : 1;
@@ -759,12 +765,11 @@ hipError_t launch_gemm(GemmArgs g, bool a_kmajor, bool beta, float* partial, int
   GemmArgs p = g;
   p.C = partial;
   p.ldc = g.N;
-  p.alpha = 1.f;
   p.k_split = kper;
   p.c_split_stride = g.M * g.N;
   p.c_vec = ((uintptr_t)partial % 16 == 0) && g.N % 4 == 0;
   if (hipError_t e = launch_units(p, fn, queues, num_cu, stream)) return e;
-  ReduceArgs r{partial, g.C, g.M, g.N, g.ldc, g.M * g.N, (int32_t)splits, g.alpha, beta};
+  ReduceArgs r{partial, g.C, g.M, g.N, g.ldc, g.M * g.N, (int32_t)splits};
   const bool vec = c_aligned && p.c_vec;
   const int64_t blocks = (g.M * g.N / (vec ? 4 : 1) + 255) / 256;
   const void* rfn = vec ? (const void*)&splitk_reduce_kernel<true>
