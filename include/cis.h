@@ -98,10 +98,10 @@ typedef struct cis_stats {
 
 /* Bytes of device workspace cis_loss_fwd/_bwd and cis_weights_ex (without sequence
  * operators) need for T rows (T >= 0). The workspace holds the cis_stats_t, the counters of
- * the fused pass's row queue (which each call clears with a kernel of its own before the rows
- * start) and per-row scratch: loss terms, flags and diagnostics, and for the forward pass the
- * partial sums of up to 32 segments per row (274 bytes per row in all); its previous contents
- * do not matter.
+ * the fused pass's row queue (which a call that uses them clears by a kernel before the rows
+ * start) and per-row scratch: loss terms, flags and diagnostics, and for the forward pass and the
+ * fused pass over few long rows the partial sums of up to 32 segments per row (274 bytes per row
+ * in all); its previous contents do not matter.
  * Returns 0 for T < 0. */
 size_t cis_workspace_bytes(int64_t T);
 

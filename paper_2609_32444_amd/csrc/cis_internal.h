@@ -197,7 +197,7 @@ struct RowArgs {
   // row queue of the row kernel (up to kRowQueues counters, kQueueStride bytes apart), or null
   // where no row comes from it: a workgroup's first three rows are fixed; with n counters in use
   // (see cis_row_kernel), counter c hands out the later rows 3*gridDim.x + c + n*q, q = 0, 1,
-  // ... Cleared by queue_reset_kernel before every launch.
+  // ... Cleared before the rows by the pre-pass, where it runs, or by queue_reset_kernel.
   unsigned long long* queue;
 };
 
@@ -227,7 +227,7 @@ inline int32_t seg_rotation(int32_t nseg, int32_t segvec, int32_t nvec) {
 constexpr int kCombineBlock = 256;
 constexpr int kSegGradBlock = 128, kSegGradK = 8;   // 16 KiB of logits per workgroup
 // A compiled segment kernel: `block` threads with K 16-byte vectors each, so block * K vectors
-// per segment.
+// per segment. SegUse is what it is for (see cis_seg_kernel).
 enum class SegUse { kPlain, kRotated, kGrad };
 struct SegVariant {
   int block, k;
@@ -236,8 +236,9 @@ struct SegVariant {
 // The segment kernel for rows of `nvec` vectors, or nullptr when the row kernel serves them
 // better (short rows) or they need more than kSegMax segments of the largest variant.
 const SegVariant* select_seg_variant(int dtype, int32_t nvec);
-// The fused pass over few long rows: cis_seg_kernel, then cis_seg_grad_kernel over the same
-// segments. `fn` is the segment kernel; null when the row kernel serves such a call better.
+// The fused pass over few long rows: cis_seg_kernel (`fn`), then cis_seg_grad_kernel (`grad`) over
+// the same segments. select_seg_grad_variant returns false, and sets nothing, when the row kernel
+// serves such a call better.
 struct SegGradVariant {
   int block, k;
   const void *fn, *grad;

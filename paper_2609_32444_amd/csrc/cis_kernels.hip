@@ -143,8 +143,8 @@ const void* combine_kernel(bool ext, bool lane) {
   return lane ? (const void*)&cis_combine_lane_kernel<false> : (const void*)&cis_combine_kernel<false>;
 }
 
-// Clears the row kernel's queue counters ahead of each launch: a kernel rather than a memset,
-// so a captured call holds no memset node.
+// Clears the row kernel's queue counters ahead of a launch that uses them, where no pre-pass does: a
+// kernel rather than a memset, so a captured call holds no memset node.
 __global__ __launch_bounds__(64) void cis_queue_reset_kernel(unsigned long long* q) {
   if (threadIdx.x < kRowQueues) q[threadIdx.x * (kQueueStride / sizeof(*q))] = 0ull;
 }
