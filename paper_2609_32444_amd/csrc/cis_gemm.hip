@@ -347,13 +347,17 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t slab_rsrc(const __bf16* p, uin
 // alone, one slab ahead, take 1.2-1.5 us per slab here, and 0.92-1.16 us two slabs ahead.
 // The same stream runs on into the next tile: its first two slabs are requested during the last
 // two of this one, so the epilogue runs with them in flight. (Past the last unit, and past the
-// end of the contraction, the loads are out of range and return zeros.) Contractions are
-// multiplied in pairs of slabs.
+// end of the contraction, the loads are out of range and return zeros.) With an odd number of
+// slabs the last odd slab's phases are left out and its pieces requested at once: 4096 x 151936 x
+// 192 430 us when they multiplied zeros, 389 so; x 576 759 and 702, x 1600 1591 and 1536.
 //
-// What bounds it: the card's power. With operands of zeros the same loop runs at 2.36 GHz and
-// 2110-2230 TFLOP/s (2290-2390 clocks per slab, 2048 of them MFMAs); with random operands the
-// clock falls to 1.67-1.71 GHz (1423-1535 TFLOP/s without an epilogue). Products of the rollout
-// batch, before (one slab ahead, every fragment read behind the slab's barrier) and now:
+// What bounds it: the card's power, and the epilogue. With operands of zeros the same loop runs at
+// 2.36 GHz and 2110-2230 TFLOP/s (2290-2390 clocks per slab, 2048 of them MFMAs); with random
+// operands and no epilogue, one after another, the clock falls to 1.67-1.71 GHz (1423-1535
+// TFLOP/s, the MFMAs busy for more than 80% of the clocks). Within a call the MFMAs are busy for less
+// (counters, a pass of its own: 68-72% for dL/dh and dL/dW, 50% for the logits with their store, whose
+// waves all store with no MFMAs to do), and the clock is higher for it: 1.98, 1.85 and 2.04 GHz.
+// Products of the rollout batch, before (one slab ahead, every fragment read behind the slab's barrier) and now:
 // logits with pairs, 4096 x 151936 x 2048, 2.07 and 1.84 ms; with the stored chunk 2.65 and
 // 2.38 ms; dL/dh, 4096 x 2048 x 151936, 1.97 and 1.79 ms (1.68 with a transposed copy of W, which
 // takes 0.22 ms per call); dL/dW, 151936 x 2048 x 16384, 8.62 and 7.39 ms (7.30 with transposed
@@ -567,6 +571,17 @@ __global__ __launch_bounds__(kThreads) void gemm_bf16_kernel(const GemmArgs g) {
       phase(1, 0, a1, b0, [&](int q) { if (q < 4) read_b(b1, 1, 1, q); },
             [&] { load(0, 1, 0, ra, k2, su.kend); });
       wait_barrier<2 * kGroupLoads>();
+      if (cur.kend - cur.kbeg <= (kt + 1) * kGemmBK) {   // no odd slab: an odd number of them
+        ra = rsrc(0, su, k3);
+        rb = rsrc(1, su, k3);
+        load(0, 0, 1, ra, k3, su.kend);
+        load(1, 1, 1, rb, k3, su.kend);
+        load(1, 0, 1, rb, k3, su.kend);
+        load(0, 1, 1, ra, k3, su.kend);
+        if (tail_nxt == 0) fix(0, su.kend);
+        wait_barrier<2 * kGroupLoads>();
+        break;
+      }
       // odd slab
       phase(0, 1, a0, b1, [&](int q) { if (q < 4) read_b(b0, 0, 1, q); },
             [&] { ra = rsrc(0, su, k3); load(0, 0, 1, ra, k3, su.kend); });
@@ -759,7 +774,7 @@ hipError_t launch_gemm_nn(GemmArgs g, float* partial, int64_t max_splits, GemmQu
     return launch_units(g, fn, queues, num_cu, stream);
   }
   // split-K: partial products into `partial` [splits][M][N], then summed in split order
-  // (whole pairs of slabs: an odd one is multiplied with a slab of zeros)
+  // (whole pairs of slabs, the unit of the loop)
   const int64_t kper =
       ((g.K + splits - 1) / splits + 2 * kGemmBK - 1) / (2 * kGemmBK) * (2 * kGemmBK);
   GemmArgs p = g;
