@@ -355,8 +355,8 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t slab_rsrc(const __bf16* p, uin
 // 2.36 GHz and 2110-2230 TFLOP/s (2290-2390 clocks per slab, 2048 of them MFMAs); with random
 // operands and no epilogue, one after another, the clock falls to 1.67-1.71 GHz (1423-1535
 // TFLOP/s, the MFMAs busy for more than 80% of the clocks). Within a call the MFMAs are busy for less
-// (counters, a pass of its own: 68-72% for dL/dh and dL/dW, 50% for the logits with their store, whose
-// waves all store with no MFMAs to do), and the clock is higher for it: 1.98, 1.85 and 2.04 GHz.
+// (counters, a pass of its own: 66% for dL/dh, 71% for dL/dW, 50% for the logits with their store,
+// whose waves all store with no MFMAs to do), and the clock is higher for it: 2.04, 1.87 and 2.12 GHz.
 // Products of the rollout batch, before (one slab ahead, every fragment read behind the slab's barrier) and now:
 // logits with pairs, 4096 x 151936 x 2048, 2.07 and 1.84 ms; with the stored chunk 2.65 and
 // 2.38 ms; dL/dh, 4096 x 2048 x 151936, 1.97 and 1.79 ms (1.68 with a transposed copy of W, which
